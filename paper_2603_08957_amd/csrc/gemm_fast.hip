@@ -1,7 +1,13 @@
 // Tile contraction for plain 2-D tiles, bf16 or fp32: each workgroup owns a
 // 128x128 block of one output tile and accumulates sum over the pairs of its
-// work unit of A_p (128 x K) * B_p (K x 128) on v_mfma_f32_32x32x16_bf16
-// (bf16) or v_mfma_f32_32x32x2_f32 (fp32).
+// work unit of A_p (128 x K) * B_p (K x 128) on v_mfma_f32_32x32x16_bf16; an
+// fp32 operand is split into three bf16 parts as its fragments are read
+// (split_f32.h), and blocks for which that does not hold are computed again on
+// v_mfma_f32_32x32x2_f32.  A block-sparse product (819 fp32 blocks of 128x128
+// times 16384x1024, 27.5 GFLOP) took 228 us on the fp32 MFMAs (121 TFLOP/s of
+// the 156 they sustain) and takes 155 us: 177 of the 220 TFLOP/s at which
+// registers alone can be split and multiplied (random values hold the bf16
+// MFMAs to 1.69 of 2.46 PFLOP/s by power).
 //
 // 256 threads = 4 waves in a 2x2 grid, each wave a 64x64 sub-block (2x2 MFMA
 // tiles, 64 fp32 accumulators per lane).  K advances over the concatenation
@@ -39,6 +45,7 @@
 // insertion would drain every outstanding copy before the first LDS read);
 // the kernel waits for them explicitly (vmcnt) before each barrier and
 // drains them before it leaves the loop.
+#include "split_f32.h"
 #include "tre_internal.h"
 
 #include <type_traits>
@@ -323,12 +330,6 @@ __device__ inline void run_unit(const FastArgs& g, const Unit& un, int m0, int n
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int wm = w >> 1, wn = w & 1;
     floatx16 acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; i++)
-#pragma unroll
-        for (int j = 0; j < 2; j++)
-#pragma unroll
-            for (int r = 0; r < 16; r++) acc[i][j][r] = 0.f;
 
     const int np = un.p1 - un.p0;
     const int tpp = g.K / kTickK<T>;  // ticks per pair
@@ -345,15 +346,6 @@ __device__ inline void run_unit(const FastArgs& g, const Unit& un, int m0, int n
         pc.at_end();
         return;
     }
-    // the pair list is read-only here; reading it through the constant
-    // address space keeps the (uniform) index loads on the scalar unit
-    Cursor<T, AROW, ANT> ca;
-    Cursor<T, BROW, BNT> cb;
-    ca.init(reinterpret_cast<const T*>(g.A) + dma_origin<AROW>(g.lda, m0, 0), (const const_i32*)(g.pa + un.p0),
-            g.a_elems, g.lda, g.K, np, lane, w);
-    cb.init(reinterpret_cast<const T*>(g.B) + dma_origin<BROW>(g.ldb, n0, 0), (const const_i32*)(g.pb + un.p0),
-            g.b_elems, g.ldb, g.K, np, lane, w);
-
     uint32_t oa[2][4], ob[2][4];
 #pragma unroll
     for (int t = 0; t < 2; t++) {
@@ -366,76 +358,134 @@ __device__ inline void run_unit(const FastArgs& g, const Unit& un, int m0, int n
         }
     }
 
-    // refills of tick tau: KFAST rings on even ticks (stage tau / 2 + 2),
-    // then RFAST rings (stage tau + 3); the prologue runs ticks -4 .. -1
-    auto refill = [&](int tau_parity, bool rf_too) {
-        if (tau_parity == 0) {
-            if (!AROW) ca.issue(lds_a, w);
-            if (!BROW) cb.issue(lds_b, w);
-        }
-        if (rf_too) {
-            if (AROW) ca.issue(lds_a, w);
-            if (BROW) cb.issue(lds_b, w);
-        }
-    };
-    refill(0, false);  // tick -4
-    refill(1, true);   // tick -3
-    refill(0, true);   // tick -2
-    refill(1, true);   // tick -1
+    // The unit's sum over its pairs into acc; with `split` an fp32 product is
+    // taken on the bf16 matrix cores (split_f32.h), `mx` collecting the largest
+    // input.
+    float mx = 0.f;
+    auto run = [&](auto split, auto& pacer) {
+        constexpr bool kSplit = decltype(split)::value;
+#pragma unroll
+        for (int i = 0; i < 2; i++)
+#pragma unroll
+            for (int j = 0; j < 2; j++)
+#pragma unroll
+                for (int r = 0; r < 16; r++) acc[i][j][r] = 0.f;
+        // the pair list is read-only here; reading it through the constant
+        // address space keeps the (uniform) index loads on the scalar unit
+        Cursor<T, AROW, ANT> ca;
+        Cursor<T, BROW, BNT> cb;
+        ca.init(reinterpret_cast<const T*>(g.A) + dma_origin<AROW>(g.lda, m0, 0), (const const_i32*)(g.pa + un.p0),
+                g.a_elems, g.lda, g.K, np, lane, w);
+        cb.init(reinterpret_cast<const T*>(g.B) + dma_origin<BROW>(g.ldb, n0, 0), (const const_i32*)(g.pb + un.p0),
+                g.b_elems, g.ldb, g.K, np, lane, w);
 
-    int sa = 0, sb = 0;  // ring stage being read
-    auto tick = [&](auto parity) {
-        constexpr int p = decltype(parity)::value;
-        __builtin_amdgcn_s_waitcnt(vmcnt_only(p == 0 ? SH::kWait0 : SH::kWait1));
-        __syncthreads();
-        refill(p, true);
-        const char* As = lds + sa * RA::kStageBytes;
-        const char* Bs = lds + RA::kBytes + sb * RB::kStageBytes;
-        if constexpr (F32) {
-            float a[2][8], b[2][8];
-#pragma unroll
-            for (int t = 0; t < 2; t++) {
-                frag8_f32<AROW>(As, oa[t], p, a[t]);
-                frag8_f32<BROW>(Bs, ob[t], p, b[t]);
+        // refills of tick tau: KFAST rings on even ticks (stage tau / 2 + 2),
+        // then RFAST rings (stage tau + 3); the prologue runs ticks -4 .. -1
+        auto refill = [&](int tau_parity, bool rf_too) {
+            if (tau_parity == 0) {
+                if (!AROW) ca.issue(lds_a, w);
+                if (!BROW) cb.issue(lds_b, w);
             }
-#pragma unroll
-            for (int s = 0; s < 8; s++) {
-                acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[0][s], b[0][s], acc[0][0], 0, 0, 0);
-                acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[0][s], b[1][s], acc[0][1], 0, 0, 0);
-                acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[1][s], b[0][s], acc[1][0], 0, 0, 0);
-                acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[1][s], b[1][s], acc[1][1], 0, 0, 0);
+            if (rf_too) {
+                if (AROW) ca.issue(lds_a, w);
+                if (BROW) cb.issue(lds_b, w);
             }
-        } else {
-            bf16x8 a[2][2], b[2][2];
-#pragma unroll
-            for (int s = 0; s < 2; s++)
+        };
+        refill(0, false);  // tick -4
+        refill(1, true);   // tick -3
+        refill(0, true);   // tick -2
+        refill(1, true);   // tick -1
+
+        Split8 fa[2][2] = {}, fb[2][2] = {};  // fp32: the split fragments of even and odd ticks
+        int sa = 0, sb = 0;  // ring stage being read
+        auto tick = [&](auto parity) {
+            constexpr int p = decltype(parity)::value;
+            __builtin_amdgcn_s_waitcnt(vmcnt_only(p == 0 ? SH::kWait0 : SH::kWait1));
+            __syncthreads();
+            refill(p, true);
+            const char* As = lds + sa * RA::kStageBytes;
+            const char* Bs = lds + RA::kBytes + sb * RB::kStageBytes;
+            if constexpr (F32 && !kSplit) {
+                float a[2][8], b[2][8];
 #pragma unroll
                 for (int t = 0; t < 2; t++) {
-                    a[s][t] = frag_read<AROW>(As, oa[t][AROW ? s : 2 * p + s]);
-                    b[s][t] = frag_read<BROW>(Bs, ob[t][BROW ? s : 2 * p + s]);
+                    frag8_f32<AROW>(As, oa[t], p, a[t]);
+                    frag8_f32<BROW>(Bs, ob[t], p, b[t]);
                 }
 #pragma unroll
-            for (int s = 0; s < 2; s++) {
-                acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s][0], b[s][0], acc[0][0], 0, 0, 0);
-                acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s][0], b[s][1], acc[0][1], 0, 0, 0);
-                acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s][1], b[s][0], acc[1][0], 0, 0, 0);
-                acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s][1], b[s][1], acc[1][1], 0, 0, 0);
+                for (int s = 0; s < 8; s++) {
+                    acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[0][s], b[0][s], acc[0][0], 0, 0, 0);
+                    acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[0][s], b[1][s], acc[0][1], 0, 0, 0);
+                    acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[1][s], b[0][s], acc[1][0], 0, 0, 0);
+                    acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[1][s], b[1][s], acc[1][1], 0, 0, 0);
+                }
+            } else if constexpr (F32) {
+                // this tick's values are split while the MFMAs of the tick
+                // before run (24 MFMAs of 32 cycles against 200 vector
+                // instructions of 4)
+                float va[2][8], vb[2][8];
+#pragma unroll
+                for (int t = 0; t < 2; t++) {
+                    frag8_f32<AROW>(As, oa[t], p, va[t]);
+                    frag8_f32<BROW>(Bs, ob[t], p, vb[t]);
+                }
+                split_mma_next(acc, fa[1 - p], fb[1 - p], va, vb, fa[p], fb[p], mx);
+            } else {
+                bf16x8 a[2][2], b[2][2];
+#pragma unroll
+                for (int s = 0; s < 2; s++)
+#pragma unroll
+                    for (int t = 0; t < 2; t++) {
+                        a[s][t] = frag_read<AROW>(As, oa[t][AROW ? s : 2 * p + s]);
+                        b[s][t] = frag_read<BROW>(Bs, ob[t][BROW ? s : 2 * p + s]);
+                    }
+#pragma unroll
+                for (int s = 0; s < 2; s++) {
+                    acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s][0], b[s][0], acc[0][0], 0, 0, 0);
+                    acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s][0], b[s][1], acc[0][1], 0, 0, 0);
+                    acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s][1], b[s][0], acc[1][0], 0, 0, 0);
+                    acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s][1], b[s][1], acc[1][1], 0, 0, 0);
+                }
             }
+            // advance the read stages: RFAST every tick, KFAST after odd ticks
+            if (AROW || p == 1) sa = sa == RA::kStages - 1 ? 0 : sa + 1;
+            if (BROW || p == 1) sb = sb == RB::kStages - 1 ? 0 : sb + 1;
+        };
+        // K is a multiple of 64, so a unit has an even number of ticks
+        for (int t = 0; t < ticks; t += 2) {
+            if (t % tpp == 0) pacer.at_pair(t / tpp);
+            tick(std::integral_constant<int, 0>{});
+            tick(std::integral_constant<int, 1>{});
         }
-        // advance the read stages: RFAST every tick, KFAST after odd ticks
-        if (AROW || p == 1) sa = sa == RA::kStages - 1 ? 0 : sa + 1;
-        if (BROW || p == 1) sb = sb == RB::kStages - 1 ? 0 : sb + 1;
+        if constexpr (F32 && kSplit) split_mma(acc, fa[1], fb[1]);
+        pacer.at_end();
+        // the copies issued past the end must land before the workgroup leaves
+        // (its LDS may be handed to another workgroup)
+        __builtin_amdgcn_s_waitcnt(vmcnt_only(0));
     };
-    // K is a multiple of 64, so a unit has an even number of ticks
-    for (int t = 0; t < ticks; t += 2) {
-        if (t % tpp == 0) pc.at_pair(t / tpp);
-        tick(std::integral_constant<int, 0>{});
-        tick(std::integral_constant<int, 1>{});
+    run(std::integral_constant<bool, F32>{}, pc);
+    if constexpr (F32) {
+        SplitCheck check;
+#pragma unroll
+        for (int i = 0; i < 2; i++)
+#pragma unroll
+            for (int j = 0; j < 2; j++)
+#pragma unroll
+                for (int r = 0; r < 16; r++) check.add(acc[i][j][r]);
+        // the waves agree through the ring's LDS, which no copy or read uses
+        // any more (no LDS of its own: two workgroups share a CU's)
+        int32_t* flag = reinterpret_cast<int32_t*>(lds);
+        const bool bad = __ballot(check.bad(mx)) != 0;
+        __syncthreads();
+        if (lane == 0) flag[w] = bad;
+        __syncthreads();
+        const bool redo = (flag[0] | flag[1] | flag[2] | flag[3]) != 0;
+        if (redo) {
+            __syncthreads();
+            NoPace none;
+            run(std::false_type{}, none);
+        }
     }
-    pc.at_end();
-    // the copies issued past the end must land before the workgroup leaves
-    // (its LDS may be handed to another workgroup)
-    __builtin_amdgcn_s_waitcnt(vmcnt_only(0));
 
     // non-temporal stores: an output block is written once per launch, and
     // keeping its lines out of L2 leaves room for the reused operand's tiles
