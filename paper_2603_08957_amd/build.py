@@ -17,7 +17,7 @@ FLAGS = [
     "-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
     # keep the compiler from forming packed fp32 instructions
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-    "-I", os.path.join(ROOT, "include"), "-Wall", "-Wno-unused-function",
+    "-I", os.path.join(ROOT, "include"), "-Wall", "-Wno-unused-function", "-Wno-inline-asm",
 ]
 
 

@@ -30,7 +30,8 @@ int64_t blocks_per_unit(const Plan& p) {
     if (p.kclass == KC_GEMM) {
         const int64_t M = p.swap ? p.nN : p.nM, N = p.swap ? p.nM : p.nN;
         if (p.fast) return (M / 128) * (N / 128);
-        return p.nB * ((M + 63) / 64) * ((N + 63) / 64);
+        const int64_t bm = 32 * p.tile_m, bn = 32 * p.tile_n;
+        return p.nB * ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
     }
     return (p.tile_elems[2] + 255) / 256;
 }
@@ -114,6 +115,8 @@ int64_t choose_unit(const Plan& p, const Layout& L, int64_t n_pairs, int64_t n_w
     int64_t pu;
     if (p.opt.max_pairs_per_unit > 0) {
         pu = p.opt.max_pairs_per_unit;
+    } else if (p.kclass == KC_GEMM && !p.fast) {
+        pu = tile_unit_pairs(p, n_pairs, n_w);
     } else if (double(n_w) * uw >= kTargetWorkgroups || (p.kclass == KC_GEMM && double(n_w) * uw >= fill)) {
         pu = std::max<int64_t>(n_pairs, 1);  // enough output blocks: one unit per key
     } else {

@@ -12,22 +12,15 @@
 // K is the EinSum over the tile labels, W[b,m,n] += sum_k A[b,m,k] B[b,k,n];
 // element offsets inside a tile come from per-role tables, so any label
 // order / layout of the operand tiles is accepted.
-//   KC_GEMM: 64x64 output block per 256-thread workgroup (2x2 waves of one
-//            32x32 MFMA tile each), 32-deep K chunks staged in LDS, the next
-//            two chunks' global loads in flight in registers;
-//            fp32 -> v_mfma_f32_32x32x2_f32, bf16 -> v_mfma_f32_32x32x16_bf16.
+//   KC_GEMM: MFMA blocks (gemm_fast.hip, gemm_tile.hip).
 //   KC_VEC : one output element per thread, fp32 FMA (scale, GEMV, dot).
 #include "tre_internal.h"
 
-#include <type_traits>
 
 namespace tre {
 
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
-typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 256;
@@ -38,8 +31,9 @@ __device__ inline float ld_f(const uint16_t* p) { return __uint_as_float(uint32_
 // ---------------------------------------------------------------- tables
 
 // off[t] < 0: the plan's contraction kernel does not read table t (the
-// GEMM class reads the A/B/W tables, the vector class the E/K ones, the
-// 128x128 path none), so it is not written.
+// GEMM class reads the W tables and, where it gathers its operands, theirs,
+// the vector class the E/K ones, the 128x128 path none), so it is not
+// written.
 struct TableSet {
     Dims d[T_COUNT];
     int64_t off[T_COUNT];
@@ -157,7 +151,11 @@ __global__ __launch_bounds__(kOrderBins) void k_order_units(Unit* __restrict__ u
 // writes the tile offset tables first (small tables only, `tables`
 // non-null), saving their launch.  With `dev_nw` the key count is the one the
 // join wrote into the header (`n_w` is then an upper bound), so the launch
-// needs no count from the host.
+// needs no count from the host.  order: 0 key by key; 1 longest first; 2 the
+// first units of all keys, then all second ones, and so on -- for keys cut
+// into units of one length, where the workgroups that run together then read
+// the same range of U's tiles (a key's pairs are in U order) and share them in
+// L2 (320 keys cut in 7 over 8 MB of U tiles: 3.3 GB fetched in key order).
 constexpr int kUnitsThreads = kOrderBins;
 constexpr int kUnitsPer = kOrderMax / kUnitsThreads;
 constexpr int64_t kUnitsTableMax = 16384;
@@ -172,6 +170,7 @@ __global__ __launch_bounds__(kUnitsThreads) void k_units_small(const int32_t* __
                                                                 WsHeader* __restrict__ hdr, TableSet ts,
                                                                 int32_t* __restrict__ tables, int dev_nw) {
     __shared__ Unit buf[kOrderMax];
+    __shared__ uint16_t ubin[kOrderMax];
     __shared__ int32_t cnt[kOrderBins];
     __shared__ int32_t wsum[kUnitsThreads / 64];
     __shared__ int32_t key_uo[kOrderMax + 1], key_po[kOrderMax], key_a[kOrderMax + 1];
@@ -298,16 +297,19 @@ __global__ __launch_bounds__(kUnitsThreads) void k_units_small(const int32_t* __
             u.p1 = a + int32_t(x1 >> 32 ? x1 / uint32_t(k) : uint32_t(x1) / uint32_t(k));
             u.slot = key_po[lo] + q;
         }
-        if (in_lds) buf[i] = u;
-        else units[i] = u;
+        if (in_lds) {
+            buf[i] = u;
+            ubin[i] = uint16_t(order == 2 ? min(q, kOrderBins - 1) : kOrderBins - 1 - min(u.p1 - u.p0, kOrderBins - 1));
+        } else {
+            units[i] = u;
+        }
     }
     if (!in_lds) return;
-    // longest first (unit lengths capped at kOrderBins - 1; order within a
-    // length class is free: a unit's sum does not depend on when it runs)
+    // counting sort by bin (the order within a bin is free: a unit's sum does
+    // not depend on when it runs)
     // (units mostly share one or two lengths, and LDS atomics on one
     // address serialise: the lanes of a wavefront with the leading lane's
     // length take one atomic together, twice; any lanes left take one each)
-    auto bin = [](const Unit& u) { return kOrderBins - 1 - min(u.p1 - u.p0, kOrderBins - 1); };
     const int lane = t & 63;
     const uint64_t below = (uint64_t(1) << lane) - 1;
     // counting pass (place false): adds the lane to its bin's count;
@@ -332,7 +334,7 @@ __global__ __launch_bounds__(kUnitsThreads) void k_units_small(const int32_t* __
     __syncthreads();
     for (int i0 = t - lane; i0 < n_units; i0 += kUnitsThreads) {
         const int i = i0 + lane;
-        (void)wave_rank(i < n_units, i < n_units ? bin(buf[i]) : 0, false);
+        (void)wave_rank(i < n_units, i < n_units ? ubin[i] : 0, false);
     }
     __syncthreads();
     int32_t total;
@@ -344,7 +346,7 @@ __global__ __launch_bounds__(kUnitsThreads) void k_units_small(const int32_t* __
         const int i = i0 + lane;
         const bool valid = i < n_units;
         const Unit u = valid ? buf[i] : Unit{};
-        const int32_t r = wave_rank(valid, valid ? bin(u) : 0, true);
+        const int32_t r = wave_rank(valid, valid ? ubin[i] : 0, true);
         if (valid) units[r] = u;
     }
 }
@@ -385,245 +387,6 @@ __global__ void k_range_units(const int32_t* __restrict__ seg_start, const int32
     u.p1 = r + 1 == R ? hi : lower(int64_t(r + 1) * n_u / R);
     u.slot = s * R + r;
     units[idx] = u;
-}
-
-// ------------------------------------------------------------------ GEMM
-
-struct GemmArgs {
-    const void* A;
-    const void* B;
-    const int32_t* pa;
-    const int32_t* pb;
-    int64_t a_elems, b_elems, w_elems;
-    const int32_t *tAM, *tAK, *tBK, *tBN, *tWM, *tWN, *tAB, *tBB, *tWB;
-    int32_t M, N, K, nB, mblocks, nblocks;
-    int32_t vec_a, vec_b;
-    const Unit* units;
-    const WsHeader* hdr;
-    float* W;
-    float* partials;
-};
-
-constexpr int kBM = 64, kBN = 64, kBK = 32;
-
-// LDS row pitches (elements).  fp32 [row][k] rows of 36 floats are 16-byte
-// aligned and a 16-lane b128 read of 16 rows at one k offset hits 16
-// distinct 4-bank groups; [k][row] rows are padded by one element.
-template <typename T>
-struct LdsPitch;
-template <>
-struct LdsPitch<float> {
-    static constexpr int kfast = kBK + 4;   // [row][k]
-    static constexpr int rfast = kBM + 1;   // [k][row]
-};
-template <>
-struct LdsPitch<uint16_t> {
-    static constexpr int kfast = kBK + 8;   // keeps 16-byte row alignment for 8-wide reads
-    static constexpr int rfast = kBM + 2;
-};
-
-// 8 consecutive elements from a 16-byte aligned address.
-__device__ inline void load8(float* v, const float* src) {
-    const uint4 a = reinterpret_cast<const uint4*>(src)[0], b = reinterpret_cast<const uint4*>(src)[1];
-    __builtin_memcpy(v, &a, 16);
-    __builtin_memcpy(v + 4, &b, 16);
-}
-__device__ inline void load8(uint16_t* v, const uint16_t* src) {
-    const uint4 a = *reinterpret_cast<const uint4*>(src);
-    __builtin_memcpy(v, &a, 16);
-}
-
-// One thread's share (8 elements) of a 64 x 32 (rows x k) chunk of one
-// operand, held in registers between its global load and its LDS store so
-// the next chunk's loads overlap the current chunk's MFMAs.
-//   KF: the operand's unit-stride dim is k (LDS [row][k]); else rows ([k][row]).
-template <typename T, bool KF>
-struct Staged {
-    T v[8];
-    // tR: element offsets of the block's rows (local index, rows < nr valid);
-    // tK: offsets of the contracted index (both tables in LDS)
-    __device__ void load(const T* __restrict__ base, const int32_t* tR, const int32_t* tK, int nr, int k0, int K,
-                         bool vec) {
-        const int t = threadIdx.x;
-        if (KF) {
-            const int lr = t >> 2, gk = k0 + (t & 3) * 8;
-            if (vec && lr < nr && gk + 8 <= K) {
-                load8(v, base + tR[lr] + tK[gk]);
-            } else {
-#pragma unroll
-                for (int j = 0; j < 8; j++) v[j] = (lr < nr && gk + j < K) ? base[tR[lr] + tK[gk + j]] : T(0);
-            }
-        } else {
-            const int gk = k0 + (t >> 3), lr = (t & 7) * 8;
-            if (vec && gk < K && lr + 8 <= nr) {
-                load8(v, base + tK[gk] + tR[lr]);
-            } else {
-#pragma unroll
-                for (int j = 0; j < 8; j++) v[j] = (gk < K && lr + j < nr) ? base[tK[gk] + tR[lr + j]] : T(0);
-            }
-        }
-    }
-    __device__ void store(T* __restrict__ lds) const {
-        const int t = threadIdx.x;
-        if (KF) {
-            T* d = lds + (t >> 2) * LdsPitch<T>::kfast + (t & 3) * 8;
-            if constexpr (sizeof(T) == 4) {
-                reinterpret_cast<f32x4*>(d)[0] = f32x4{v[0], v[1], v[2], v[3]};
-                reinterpret_cast<f32x4*>(d)[1] = f32x4{v[4], v[5], v[6], v[7]};
-            } else {
-#pragma unroll
-                for (int j = 0; j < 8; j++) d[j] = v[j];
-            }
-        } else {
-            T* d = lds + (t >> 3) * LdsPitch<T>::rfast + (t & 7) * 8;
-#pragma unroll
-            for (int j = 0; j < 8; j++) d[j] = v[j];
-        }
-    }
-};
-
-template <bool KF>
-__device__ inline bf16x8 frag_bf16(const uint16_t* lds, int row, int k) {
-    u16x8 v;
-    if (KF) {
-        v = *reinterpret_cast<const u16x8*>(lds + row * LdsPitch<uint16_t>::kfast + k);
-    } else {
-#pragma unroll
-        for (int j = 0; j < 8; j++) v[j] = lds[(k + j) * LdsPitch<uint16_t>::rfast + row];
-    }
-    return __builtin_bit_cast(bf16x8, v);
-}
-
-// fp32 operand values of 4 consecutive MFMA k-steps (k = k4 .. k4 + 3) for
-// the lane's row: one 16-byte read from [row][k], four reads from [k][row].
-template <bool KF>
-__device__ inline f32x4 frag4_f32(const float* lds, int row, int k4) {
-    if (KF) return *reinterpret_cast<const f32x4*>(lds + row * LdsPitch<float>::kfast + k4);
-    f32x4 v;
-#pragma unroll
-    for (int j = 0; j < 4; j++) v[j] = lds[(k4 + j) * LdsPitch<float>::rfast + row];
-    return v;
-}
-
-// PF: load two chunks ahead (worth it for long units; short units keep the
-// registers and get more workgroups per CU instead).
-template <typename T, bool AK, bool BK, bool PF>
-__global__ __launch_bounds__(kThreads) void k_gemm(GemmArgs g) {
-    const int64_t n_units = g.hdr->n_units;
-    if (blockIdx.x >= n_units) return;
-    int y = blockIdx.y;
-    const int nblk = y % g.nblocks;
-    y /= g.nblocks;
-    const int mblk = y % g.mblocks;
-    const int b = y / g.mblocks;
-    const int m0 = mblk * kBM, n0 = nblk * kBN;
-
-    constexpr int kAs = AK ? kBM * LdsPitch<T>::kfast : kBK * LdsPitch<T>::rfast;
-    constexpr int kBs = BK ? kBN * LdsPitch<T>::kfast : kBK * LdsPitch<T>::rfast;
-    __shared__ __attribute__((aligned(16))) T As[kAs];
-    __shared__ __attribute__((aligned(16))) T Bs[kBs];
-
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int wm = w >> 1, wn = w & 1;
-    floatx16 acc;
-#pragma unroll
-    for (int r = 0; r < 16; r++) acc[r] = 0.f;
-
-    // offset tables of this block's rows and of the contracted index, copied
-    // to LDS once so the loads of the chunk loop depend on no global read
-    extern __shared__ int32_t tabs[];  // [kBM rows of A][kBN rows of B][K of A][K of B]
-    int32_t* sAM = tabs;
-    int32_t* sBN = tabs + kBM;
-    int32_t* sAK = tabs + kBM + kBN;
-    int32_t* sBK = sAK + g.K;
-    for (int i = threadIdx.x; i < kBM; i += kThreads) sAM[i] = m0 + i < g.M ? g.tAM[m0 + i] : 0;
-    for (int i = threadIdx.x; i < kBN; i += kThreads) sBN[i] = n0 + i < g.N ? g.tBN[n0 + i] : 0;
-    for (int i = threadIdx.x; i < g.K; i += kThreads) {
-        sAK[i] = g.tAK[i];
-        sBK[i] = g.tBK[i];
-    }
-    __syncthreads();
-    const int nra = min(kBM, g.M - m0), nrb = min(kBN, g.N - n0);
-
-    const T* Ag = reinterpret_cast<const T*>(g.A);
-    const T* Bg = reinterpret_cast<const T*>(g.B);
-    const int32_t offAB = g.tAB[b], offBB = g.tBB[b];
-    // output offset of this lane's accumulator r (the block is fixed); short
-    // units (no prefetch) keep them in registers across units
-    const int n = n0 + wn * 32 + (lane & 31);
-    auto w_offset = [&](int r) {
-        const int m = m0 + wm * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
-        return (m < g.M && n < g.N) ? g.tWB[b] + g.tWM[m] + g.tWN[n] : -1;
-    };
-    int32_t wofs[PF ? 1 : 16];
-    if constexpr (!PF) {
-#pragma unroll
-        for (int r = 0; r < 16; r++) wofs[r] = w_offset(r);
-    }
-    const int kcn = (g.K + kBK - 1) / kBK;
-    // without prefetch (short units) the grid may be smaller than the unit
-    // count: a workgroup takes units blockIdx.x, blockIdx.x + gridDim.x, ...
-    // (tables loaded once); with prefetch the grid covers every unit
-    const int64_t unit_step = PF ? n_units : int64_t(gridDim.x);
-    for (int64_t unit_id = blockIdx.x; unit_id < n_units; unit_id += unit_step) {
-        const Unit un = g.units[unit_id];
-#pragma unroll
-        for (int r = 0; r < 16; r++) acc[r] = 0.f;
-        // chunk c of the unit: pair p0 + c / kcn, k offset (c % kcn) * kBK; with
-        // PF two chunks are loaded ahead into two register sets used alternately
-        // (the LDS tile stays single, so many workgroups fit on a CU)
-        const int total = (un.p1 - un.p0) * kcn;
-        Staged<T, AK> sa[PF ? 2 : 1];
-        Staged<T, BK> sb[PF ? 2 : 1];
-        auto load = [&](int c, auto slot) {
-            constexpr int q = decltype(slot)::value;
-            const int p = un.p0 + c / kcn, k0 = (c % kcn) * kBK;
-            sa[q].load(Ag + int64_t(g.pa[p]) * g.a_elems + offAB, sAM, sAK, nra, k0, g.K, g.vec_a);
-            sb[q].load(Bg + int64_t(g.pb[p]) * g.b_elems + offBB, sBN, sBK, nrb, k0, g.K, g.vec_b);
-        };
-        const int row = lane & 31, half = lane >> 5;
-        auto step = [&](int c, auto slot) {
-            constexpr int q = decltype(slot)::value;
-            if (!PF) load(c, slot);
-            sa[q].store(As);
-            sb[q].store(Bs);
-            __syncthreads();
-            if (PF && c + 2 < total) load(c + 2, slot);
-            if constexpr (sizeof(T) == 4) {
-                // k-steps are taken in the order k = 16 half + s (s = 0 .. 15) in
-                // both operands, so a lane's k run is contiguous
-#pragma unroll
-                for (int s4 = 0; s4 < kBK / 2; s4 += 4) {
-                    const f32x4 a = frag4_f32<AK>(As, wm * 32 + row, 16 * half + s4);
-                    const f32x4 bb = frag4_f32<BK>(Bs, wn * 32 + row, 16 * half + s4);
-#pragma unroll
-                    for (int j = 0; j < 4; j++) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[j], bb[j], acc, 0, 0, 0);
-                }
-            } else {
-#pragma unroll
-                for (int ks = 0; ks < kBK; ks += 16) {
-                    bf16x8 a = frag_bf16<AK>(reinterpret_cast<const uint16_t*>(As), wm * 32 + row, ks + half * 8);
-                    bf16x8 bb = frag_bf16<BK>(reinterpret_cast<const uint16_t*>(Bs), wn * 32 + row, ks + half * 8);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bb, acc, 0, 0, 0);
-                }
-            }
-            __syncthreads();
-        };
-        using S0 = std::integral_constant<int, 0>;
-        using S1 = std::integral_constant<int, PF ? 1 : 0>;
-        if (PF && total > 0) load(0, S0{});
-        if (PF && total > 1) load(1, S1{});
-        for (int c = 0; c < total; c += 2) {
-            step(c, S0{});
-            if (c + 1 < total) step(c + 1, S1{});
-        }
-        float* out = un.slot < 0 ? g.W + int64_t(un.seg) * g.w_elems : g.partials + int64_t(un.slot) * g.w_elems;
-#pragma unroll
-        for (int r = 0; r < 16; r++) {
-            const int32_t o = PF ? w_offset(r) : wofs[r];
-            if (o >= 0) out[o] = acc[r];
-        }
-    }
 }
 
 // ------------------------------------------------------------------- VEC
@@ -919,29 +682,6 @@ __global__ void k_write_pairs(const int32_t* __restrict__ pu, const int32_t* __r
 
 inline unsigned blocks_for(int64_t n) { return unsigned((n + kThreads - 1) / kThreads); }
 
-template <typename T, bool PF>
-hipError_t gemm_dispatch(const Plan& p, const GemmArgs& g, dim3 grid, hipStream_t s) {
-    // about 16 workgroups per CU; beyond that a workgroup loops over (short) units
-    constexpr unsigned kGemmGrid = 4096;
-    if (!PF) grid.x = std::min<unsigned>(grid.x, std::max<unsigned>(1, kGemmGrid / grid.y));
-    const size_t tab = sizeof(int32_t) * size_t(kBM + kBN + 2 * int64_t(g.K));
-    if (tab > 96 * 1024) return hipErrorInvalidConfiguration;
-    const dim3 block{unsigned(kThreads)};
-    if (p.a_kfast && p.b_kfast) return launch_k(k_gemm<T, true, true, PF>, grid, block, tab, s, g);
-    if (p.a_kfast) return launch_k(k_gemm<T, true, false, PF>, grid, block, tab, s, g);
-    if (p.b_kfast) return launch_k(k_gemm<T, false, true, PF>, grid, block, tab, s, g);
-    return launch_k(k_gemm<T, false, false, PF>, grid, block, tab, s, g);
-}
-
-// Prefetch pays when units run many K chunks (pairs per unit x chunks per pair).
-template <typename T>
-hipError_t gemm_dispatch(const Plan& p, const GemmArgs& g, dim3 grid, int64_t n_pairs, int64_t n_units,
-                         hipStream_t s) {
-    const int64_t chunks = (p.nK + kBK - 1) / kBK;
-    const bool pf = n_pairs * chunks >= 4 * std::max<int64_t>(n_units, 1);
-    return pf ? gemm_dispatch<T, true>(p, g, grid, s) : gemm_dispatch<T, false>(p, g, grid, s);
-}
-
 }  // namespace
 
 namespace {
@@ -949,7 +689,9 @@ namespace {
 // Whether the plan's contraction kernel reads offset table t.
 bool table_used(const Plan& p, int t) {
     if (p.kclass == KC_VEC) return t >= T_EU;
-    return !p.fast && t < T_EU;
+    if (p.fast || t >= T_EU) return false;
+    if (t == T_AM || t == T_AK || t == T_BN || t == T_BK) return p.tile_op[0].mode == TM_GATHER;
+    return true;
 }
 
 // The tables the contraction reads (the others marked off = -1), their
@@ -1018,7 +760,9 @@ hipError_t launch_units(const Plan& p, const Layout& L, char* ws, int64_t n_pair
         const bool with_tables = total > 0 && total <= kUnitsTableMax;
         if (total > kUnitsTableMax && (e = launch_tables(p, tables, s)) != hipSuccess) return e;
         k_units_small<<<1, kUnitsThreads, 0, s>>>(seg_start, n_w, std::max<int64_t>(p_unit, 1),
-                                                   longest_first && p.kclass == KC_GEMM ? 1 : 0,
+                                                   !longest_first || p.kclass != KC_GEMM ? 0
+                                                   : !p.fast && p_unit < n_pairs         ? 2
+                                                                                         : 1,
                                                    reinterpret_cast<Unit*>(ws + L.unit_desc),
                                                    reinterpret_cast<int32_t*>(ws + L.split_list), nparts, hdr, ts,
                                                    with_tables ? tables : nullptr, dev_counts ? 1 : 0);
@@ -1076,42 +820,7 @@ hipError_t launch_contract(const Plan& p, const Layout& L, char* ws, const void*
     float* parts = reinterpret_cast<float*>(ws + L.partials);
     if (p.kclass == KC_GEMM && p.fast)
         return launch_gemm_fast(p, L, ws, u_tiles, v_tiles, w_tiles, n_pairs, unit_bound, s);
-    if (p.kclass == KC_GEMM) {
-        GemmArgs g{};
-        g.A = p.swap ? v_tiles : u_tiles;
-        g.B = p.swap ? u_tiles : v_tiles;
-        g.pa = p.swap ? pv : pu;
-        g.pb = p.swap ? pu : pv;
-        g.a_elems = p.tile_elems[p.swap ? 1 : 0];
-        g.b_elems = p.tile_elems[p.swap ? 0 : 1];
-        g.w_elems = p.tile_elems[2];
-        g.tAM = tb + p.table_off[T_AM];
-        g.tAK = tb + p.table_off[T_AK];
-        g.tBK = tb + p.table_off[T_BK];
-        g.tBN = tb + p.table_off[T_BN];
-        g.tWM = tb + p.table_off[T_WM];
-        g.tWN = tb + p.table_off[T_WN];
-        g.tAB = tb + p.table_off[T_AB];
-        g.tBB = tb + p.table_off[T_BB];
-        g.tWB = tb + p.table_off[T_WB];
-        g.M = int32_t(p.swap ? p.nN : p.nM);
-        g.N = int32_t(p.swap ? p.nM : p.nN);
-        g.K = int32_t(p.nK);
-        g.nB = int32_t(p.nB);
-        g.mblocks = (g.M + kBM - 1) / kBM;
-        g.nblocks = (g.N + kBN - 1) / kBN;
-        g.vec_a = p.vec_a;
-        g.vec_b = p.vec_b;
-        g.units = units;
-        g.hdr = hdr;
-        g.W = w_tiles;
-        g.partials = parts;
-        const int64_t gy = int64_t(g.nB) * g.mblocks * g.nblocks;
-        if (gy > 65535) return hipErrorInvalidConfiguration;
-        dim3 grid{unsigned(unit_bound), unsigned(gy), 1u};
-        return p.dtype == TRE_BF16 ? gemm_dispatch<uint16_t>(p, g, grid, n_pairs, unit_bound, s)
-                                   : gemm_dispatch<float>(p, g, grid, n_pairs, unit_bound, s);
-    }
+    if (p.kclass == KC_GEMM) return launch_gemm_tile(p, L, ws, u_tiles, v_tiles, w_tiles, n_pairs, unit_bound, s);
     // with vec_swap the kernel's first (vector) operand is V: the product is
     // symmetric, so only the roles of the pointers and tables change
     const bool sw = p.vec_swap;

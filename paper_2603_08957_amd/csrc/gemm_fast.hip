@@ -45,6 +45,7 @@
 // insertion would drain every outstanding copy before the first LDS read);
 // the kernel waits for them explicitly (vmcnt) before each barrier and
 // drains them before it leaves the loop.
+#include "lds_copy.h"
 #include "split_f32.h"
 #include "tre_internal.h"
 
@@ -80,7 +81,6 @@ struct FastArgs {
 
 typedef short v4i16 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) v4i16 lds_v4i16;
-typedef __attribute__((address_space(3))) char lds_char;
 typedef __attribute__((address_space(4))) int32_t const_i32;
 
 // s_waitcnt immediate: vmcnt(n) with expcnt and lgkmcnt left alone
@@ -99,22 +99,6 @@ struct Ring {
 // K of one tick of the main loop
 template <typename T>
 constexpr int kTickK = 64 / int(sizeof(T));
-
-__device__ inline uint64_t uniform64(uint64_t x) {
-    const uint32_t lo = __builtin_amdgcn_readfirstlane(uint32_t(x));
-    const uint32_t hi = __builtin_amdgcn_readfirstlane(uint32_t(x >> 32));
-    return (uint64_t(hi) << 32) | lo;
-}
-
-template <bool NT>
-__device__ inline void dma16(uint32_t lds_addr, const void* base, uint32_t voff) {
-    const uint32_t m = __builtin_amdgcn_readfirstlane(lds_addr);
-    const uint64_t b = uniform64(reinterpret_cast<uint64_t>(base));
-    if constexpr (NT)
-        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(m), "v"(voff), "s"(b) : "m0");
-    else
-        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(m), "v"(voff), "s"(b) : "m0");
-}
 
 // Byte offset, from the stage's chunk origin, of the 16 bytes this lane
 // copies for copy instruction q of an operand with leading dimension ld
@@ -243,7 +227,7 @@ struct Cursor {
     __device__ void issue(uint32_t ring_lds, int w) {
         const uint32_t l0 = ring_lds + stage * R::kStageBytes + R::kPerWave * w * 1024;
 #pragma unroll
-        for (int j = 0; j < R::kPerWave; j++) dma16<NT>(l0 + j * 1024, cur, src[j]);
+        for (int j = 0; j < R::kPerWave; j++) lds_copy16<NT>(l0 + j * 1024, cur, src[j]);
         stage = stage == R::kStages - 1 ? 0 : stage + 1;
         if (++ik < per_pair) {
             cur += step;
@@ -429,7 +413,7 @@ __device__ inline void run_unit(const FastArgs& g, const Unit& un, int m0, int n
                     frag8_f32<AROW>(As, oa[t], p, va[t]);
                     frag8_f32<BROW>(Bs, ob[t], p, vb[t]);
                 }
-                split_mma_next(acc, fa[1 - p], fb[1 - p], va, vb, fa[p], fb[p], mx);
+                split_mma_next(acc, fa[1 - p], fb[1 - p], va, vb, fa[p], fb[p], mx, [] {});
             } else {
                 bf16x8 a[2][2], b[2][2];
 #pragma unroll

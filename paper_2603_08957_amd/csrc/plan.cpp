@@ -130,23 +130,6 @@ static std::vector<int32_t> host_table(const Dims& d) {
     return t;
 }
 
-// True when the table is made of aligned runs of 8 consecutive offsets.
-static bool runs_of_8(const std::vector<int32_t>& t) {
-    if (t.size() % 8) return false;
-    for (size_t g = 0; g < t.size(); g += 8) {
-        if (t[g] % 8) return false;
-        for (int j = 1; j < 8; j++)
-            if (t[g + j] != t[g] + j) return false;
-    }
-    return true;
-}
-
-static bool all_mult_8(const std::vector<int32_t>& t) {
-    for (int32_t x : t)
-        if (x % 8) return false;
-    return true;
-}
-
 static tre_status classify(Plan& p) {
     // ---- join key (join labels in V's key order) ----
     p.n_join = 0;
@@ -341,19 +324,9 @@ static tre_status classify(Plan& p) {
             p.vec_swap = true;
         }
     }
-    // GEMM staging: which dim of A / B has unit stride, and whether 8-wide
-    // aligned vector loads along it are legal
     if (p.kclass == KC_GEMM) {
         auto tAM = host_table(p.dims[T_AM]), tAK = host_table(p.dims[T_AK]), tBK = host_table(p.dims[T_BK]),
              tBN = host_table(p.dims[T_BN]), tAB = host_table(p.dims[T_AB]), tBB = host_table(p.dims[T_BB]);
-        auto has_unit = [](const std::vector<int32_t>& t) { return t.size() > 1 && t[1] - t[0] == 1; };
-        p.a_kfast = has_unit(tAK) || !has_unit(tAM);
-        p.b_kfast = has_unit(tBK) || !has_unit(tBN);
-        bool te_a = p.tile_elems[A] % 8 == 0, te_b = p.tile_elems[B] % 8 == 0;
-        p.vec_a = te_a && all_mult_8(tAB) &&
-                  (p.a_kfast ? (runs_of_8(tAK) && all_mult_8(tAM)) : (runs_of_8(tAM) && all_mult_8(tAK)));
-        p.vec_b = te_b && all_mult_8(tBB) &&
-                  (p.b_kfast ? (runs_of_8(tBK) && all_mult_8(tBN)) : (runs_of_8(tBN) && all_mult_8(tBK)));
         // Fast path: bf16 (K a multiple of 64) or fp32 (K a multiple of 32),
         // no batch, 128-multiple M/N, every operand a plain 2-D row-major
         // matrix (one unit stride, one leading dimension) and W stored with N
@@ -383,6 +356,43 @@ static tre_status classify(Plan& p) {
             ok = ok && p.fast_lda % 8 == 0 && p.fast_ldb % 8 == 0;
         }
         p.fast = ok;
+        // Other shapes: blocks of up to two 32-wide MFMA tiles each way, and
+        // the widest copies each operand allows (see gemm_tile.hip; k_chunk is
+        // the contracted extent of one copy).
+        p.tile_m = M > 32 ? 2 : 1;
+        p.tile_n = N > 32 ? 2 : 1;
+        const int64_t k_chunk = p.dtype == TRE_BF16 ? 32 : 16;
+        auto operand = [&](TileOperand& o, const std::vector<int32_t>& tR, const std::vector<int32_t>& tK,
+                           const std::vector<int32_t>& tB, int64_t elems) {
+            int64_t sr, sk;
+            o = TileOperand{};
+            if (!affine(tR, sr) || !affine(tK, sk)) return;
+            o.sr = int32_t(sr);
+            o.sk = int32_t(sk);
+            // whether every offset the kernel forms is a multiple of `bytes`
+            const int64_t esz = p.dtype == TRE_BF16 ? 2 : 4;
+            auto on = [&](int64_t bytes) {
+                bool ok = elems * esz % bytes == 0;
+                for (int32_t x : tB) ok = ok && int64_t(x) * esz % bytes == 0;
+                const int64_t line = sk == 1 ? sr : sk, run = sk == 1 ? p.nK : int64_t(tR.size());
+                return ok && line * esz % bytes == 0 && run * esz % bytes == 0;
+            };
+            if (sk == 1) o.mode = on(4) ? TM_K_RUN : p.nK >= k_chunk ? TM_K_ODD : TM_GATHER;
+            else if (sr == 1 && on(4)) o.mode = TM_ROWS;
+            o.wide = on(16) && (o.mode == TM_ROWS || p.nK >= k_chunk);
+        };
+        p.tile_w_affine = affine(tWM, sWM) && affine(tWN, sWN) && sWN == 1;
+        p.tile_w_sm = sWM;
+        operand(p.tile_op[0], tAM, tAK, tAB, p.tile_elems[A]);
+        operand(p.tile_op[1], tBN, tBK, tBB, p.tile_elems[B]);
+        // the pairs of ways that are built: through LDS both ways, odd runs
+        // (which even ones are a case of) both, else the tables for both
+        TileOperand &x = p.tile_op[0], &y = p.tile_op[1];
+        auto staged = [](const TileOperand& o) { return o.mode == TM_K_RUN || o.mode == TM_ROWS; };
+        if (!(staged(x) && staged(y))) {
+            auto run = [&](const TileOperand& o) { return o.mode == TM_K_ODD || (o.mode == TM_K_RUN && p.nK >= k_chunk); };
+            x.mode = y.mode = run(x) && run(y) ? TM_K_ODD : TM_GATHER;
+        }
     }
     return TRE_OK;
 }

@@ -78,10 +78,11 @@ __device__ inline void split_mma(split_f32x16 (&acc)[TM][TN], const Split8 (&a)[
 // The MFMAs of (a, b) with the splitting of the next fragments (raw values va,
 // vb into na, nb) between them: a vector instruction issues while an MFMA
 // runs, in one order that the compiler keeps, so a wavefront alone fills both.
-template <int TM, int TN>
+// `mid` runs once the raw values are there.
+template <int TM, int TN, typename Mid>
 __device__ inline void split_mma_next(split_f32x16 (&acc)[TM][TN], const Split8 (&a)[TM], const Split8 (&b)[TN],
                                       const float (&va)[TM][8], const float (&vb)[TN][8], Split8 (&na)[TM],
-                                      Split8 (&nb)[TN], float& mx) {
+                                      Split8 (&nb)[TN], float& mx, Mid mid) {
     constexpr int kSteps = kSplitSteps<TM, TN>, kPairs = 4 * (TM + TN);
     constexpr int kLead = TM * TN;  // MFMAs that cover the latency of the raw values' reads
 #pragma unroll
@@ -89,6 +90,10 @@ __device__ inline void split_mma_next(split_f32x16 (&acc)[TM][TN], const Split8 
         split_mma_step(s, acc, a, b);
         __builtin_amdgcn_sched_barrier(0);
         if (s < kLead) continue;
+        if (s == kLead) {
+            mid();
+            __builtin_amdgcn_sched_barrier(0);
+        }
         const int p0 = (s - kLead) * kPairs / (kSteps - kLead), p1 = (s - kLead + 1) * kPairs / (kSteps - kLead);
 #pragma unroll
         for (int p = p0; p < p1; p++) {

@@ -73,6 +73,14 @@ enum TableId { T_AM, T_AK, T_BK, T_BN, T_WM, T_WN, T_AB, T_BB, T_WB, T_EU, T_EV,
 
 enum KernelClass { KC_GEMM = 0, KC_VEC = 1 };
 
+// How k_gemm_tile loads an operand (see gemm_tile.hip).
+enum TileMode { TM_GATHER = 0, TM_K_RUN = 1, TM_K_ODD = 2, TM_ROWS = 3 };
+struct TileOperand {
+    int32_t mode = TM_GATHER;
+    bool wide = false;       // 16-byte copies
+    int32_t sr = 0, sk = 0;  // offset = row * sr + k * sk (but for GATHER: the offset tables)
+};
+
 struct Plan {
     std::string einsum;
     tre_dtype dtype = TRE_F32;
@@ -107,10 +115,12 @@ struct Plan {
     int64_t nB = 1, nM = 1, nN = 1, nK = 1;
     KernelClass kclass = KC_VEC;
     bool swap = false;     // GEMM: A operand is V
-    bool a_kfast = false;  // GEMM: A's unit-stride dim is a K dim
-    bool b_kfast = false;
-    bool vec_a = false;    // GEMM: 8-wide vector loads legal along A's fast dim
-    bool vec_b = false;
+    // GEMM outside the 128x128 path: MFMA tiles (32 rows or columns) of a
+    // wavefront's block and how A and B are loaded
+    int tile_m = 2, tile_n = 2;
+    TileOperand tile_op[2];
+    bool tile_w_affine = false;  // W(m, n) at m * tile_w_sm + n
+    int64_t tile_w_sm = 0;
     // 128x128 fast path (bf16, fp32): A(m,k) = A[k*lda + m] if a_rowfast else A[m*lda + k];
     // B(n,k) = B[k*ldb + n] if b_rowfast else B[n*ldb + k]; W(m,n) = W[m*ldw + n]
     // vector class: W elements per thread (1, 4 for fp32, 8 for bf16) and
@@ -244,6 +254,11 @@ hipError_t launch_range_units(const Plan& p, const Layout& L, char* ws, int64_t 
                               hipStream_t s);
 hipError_t launch_contract(const Plan& p, const Layout& L, char* ws, const void* u_tiles, const void* v_tiles,
                            float* w_tiles, int64_t n_pairs, int64_t n_w, int64_t unit_bound, hipStream_t s);
+// gemm_tile.hip: the GEMM class outside the 128x128 path.  tile_unit_pairs:
+// the unit length for n_pairs pairs of n_w keys.
+int64_t tile_unit_pairs(const Plan& p, int64_t n_pairs, int64_t n_w);
+hipError_t launch_gemm_tile(const Plan& p, const Layout& L, char* ws, const void* u_tiles, const void* v_tiles,
+                            float* w_tiles, int64_t n_pairs, int64_t unit_bound, hipStream_t s);
 hipError_t launch_gemm_fast(const Plan& p, const Layout& L, char* ws, const void* u_tiles, const void* v_tiles,
                             float* w_tiles, int64_t n_pairs, int64_t unit_bound, hipStream_t s);
 // Persistent paced variant (one unit per key, one 128x128 block per W tile):

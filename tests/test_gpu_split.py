@@ -14,6 +14,9 @@ SHAPES = {
     "gemm128_krow": ("ik,kn->in", "ik", {"i": 128, "k": 256, "n": 128}, {"i": 128, "k": 128}),
     "gemm128_row_row": ("ki,kn->in", "ik", {"i": 128, "k": 64, "n": 256}, {"i": 128, "k": 32}),
     "gemm128_k_k": ("ik,nk->in", "ik", {"i": 128, "k": 64, "n": 128}, {"i": 128, "k": 32}),
+    "tile_krun_rows": ("ik,kn->in", "ik", {"i": 120, "k": 80, "n": 70}, {"i": 40, "k": 40}),
+    "tile_rows_krun": ("ki,nk->in", "ik", {"i": 100, "k": 102, "n": 33}, {"i": 50, "k": 51}),
+    "tile_gather_short_k": ("ik,kn->in", "ik", {"i": 51, "k": 27, "n": 17}, {"i": 17, "k": 9}),
 }
 
 
