@@ -16,35 +16,31 @@
 // matrix [M rows = U's other tile labels] x [tp * tq], and one triple
 // contributes T (M x tp*tq) times the Khatri-Rao block KR[(p', q'), r] =
 // P[p', r] * Q[q', r], P being the operand joined on p and Q the one joined
-// on q.  k3_gemm computes that with fp32 MFMA (v_mfma_f32_16x16x4f32) per
-// 32 x 64 output block: T is streamed through LDS in chunks of 128
-// contracted elements (two stages, prefetched one chunk ahead in
-// registers), P and Q of the triple are staged in LDS (Q transposed), and
-// the B operand of each MFMA is formed in registers as P * Q, so KR is never
-// stored.  When tq is 16, 32 or 64, k3_gemm_q is used instead: it contracts
-// over q' with MFMA (Q held in registers for the whole triple) and scales by
-// P[p', r] afterwards, one multiply-add per output element and p' (measured
-// 0.52 ms against 0.63 ms for k3_gemm on the 4096^3 sparse 3-way workload).
+// on q.  k3_gemm forms no Khatri-Rao block: for every p' it contracts over q'
+// only, Y[m, r] = sum_q' T[m, p', q'] Q[q', r], on the bf16 matrix cores with
+// both operands split into three parts (split_f32.h), and adds P[p', r] Y[m, r]
+// to its 32 x 64 output block (one multiply-add per element and p').
 // The triples are dealt to the resident workgroups in equal
 // contiguous ranges; a workgroup accumulates each segment's part of its range
 // in registers, and segments split between ranges are summed by k3_reduce in
 // range order (no atomics on values).
+#include "lds_copy.h"
+#include "split_f32.h"
 #include "tre_internal.h"
 
 #include <algorithm>
 #include <cstring>
+#include <type_traits>
 
 namespace tre {
 
 namespace {
 
-typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef split_f32x16 floatx16;
 
 constexpr int kThreads = 256;
 constexpr int kRows = 32;              // output rows (m) per workgroup
 constexpr int kCols = 64;              // output columns (r) per workgroup
-constexpr int kChunk = 128;            // contracted elements per staged chunk
-constexpr int kPitchT = kChunk + 4;    // floats per staged T row
 constexpr int kMaxPQ = 64;             // tile extent limit of p and q
 constexpr int kMaxRows = kMaxDims - 2; // row labels of U
 
@@ -250,16 +246,253 @@ struct Dest {
 // The workgroup holding item x.
 __device__ inline int64_t wg_of(int64_t x, int64_t total, int64_t n_wg) { return ((x + 1) * n_wg - 1) / total; }
 
-// Walk this workgroup's pieces: begin(mb, rb) before a piece, triple(t,
-// t_next) for each of its triples (t_next = the piece's next triple or -1),
-// end(Dest) after it.
-template <typename Begin, typename Triple, typename End>
-__device__ inline void for_each_piece(const F3Args& g, Begin begin, Triple triple, End end) {
+// A wavefront takes every fourth p' of each triple of the workgroup's range,
+// the whole 32 x 64 block each time, so a T element is read, split and
+// multiplied by one wavefront only.  Its T chunks (32 rows x the q' of one p')
+// run through a private ring of three LDS stages (global_load_lds; 16-byte
+// granule g of row r in slot g ^ swizzle(r), so that 16 rows at one granule
+// meet all banks), ahead across triples, with no barrier.  Q and P of a triple
+// are copied for the workgroup one triple ahead, a barrier per triple; Q's
+// fragments are split once per triple and stay in registers.  The MFMAs of one
+// 16-q' step run with the splitting of the next step's T values and the
+// scale-adds of the p' before between them.  A piece's sums over the four
+// wavefronts are added through LDS in wavefront order.
+//
+// Bound: 10,486 blocks of 32^3 against 64 columns read 1.34 GB, 200 us at the
+// 6.9 TB/s a read-mostly stream reaches, and take 260 us (169 TFLOP/s); on the
+// fp32 MFMAs (16x16x4 tiles, T staged through registers) they took 390 us.
+// 5,000 blocks of 20^3 against 83 columns: whole call 339 -> 212 us.
+constexpr int kRing = 3;
+
+// 16-byte granules of a staged T row, KS steps of 16 q'
+template <int KS>
+constexpr int kGran = KS == 1 ? 4 : KS == 2 ? 8 : 16;
+
+size_t gemm_lds_bytes(const F3Desc& d) {
+    const int ks = (d.tq + 15) / 16, gran = ks == 1 ? 4 : ks == 2 ? 8 : 16;
+    return size_t(kThreads / 64 * kRing * kRows * gran * 16) + 2 * std::max<size_t>(size_t(d.tq + d.tp) * 256, 16384);
+}
+
+template <int KS, bool FULL>
+__global__ __launch_bounds__(kThreads, KS <= 2 ? 2 : 1) void k3_gemm(F3Args g) {
+    constexpr int PG = kGran<KS>, kStage = kRows * PG * 16, kCopies = kStage / 1024;
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
     const F3Desc& d = g.d;
+    const int lane = threadIdx.x & 63, half = lane >> 5, c = lane & 31;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tq = FULL ? 16 * KS : d.tq, tp = d.tp;
+    const int ns = tp > w ? (tp - w + 3) / 4 : 0;  // this wavefront's p' of a triple
+    const int64_t KK = int64_t(tp) * tq;
+    const int qp_bytes = max((tq + tp) * 256, 16384);
+    char* ring = lds + w * (kRing * kStage);
+    char* qp = lds + (kThreads / 64) * kRing * kStage;
+    const uint32_t ring_lds = __builtin_amdgcn_readfirstlane(lds_address(ring));
+    const uint32_t qp_lds = __builtin_amdgcn_readfirstlane(lds_address(qp));
+
     const int64_t total = g.nt * int64_t(g.mblocks) * d.rblocks;
-    const int64_t b = blockIdx.x;
-    const int64_t i1 = (b + 1) * total / g.n_wg;
-    for (int64_t i = b * total / g.n_wg; i < i1;) {
+    const int64_t i0 = int64_t(blockIdx.x) * total / g.n_wg, i1 = (int64_t(blockIdx.x) + 1) * total / g.n_wg;
+    if (i0 >= i1) return;
+
+    auto swizzle = [](int row) { return PG == 4 ? (row >> 2) & 3 : PG == 8 ? (row >> 1) & 7 : row & 15; };
+    // ---- T ring: the next chunk to copy is step ci of item cx (block row cm, triple ct)
+    int64_t cx = i0;
+    int32_t ct = int32_t(i0 % g.nt), ctu = g.tu[ct];
+    int cblk = int(i0 / g.nt), ci = 0, cstage = 0;
+    int64_t crow = 0;
+    uint32_t src[kCopies];
+    auto sources = [&]() {
+        const int64_t row0 = int64_t(cblk / d.rblocks) * kRows;
+        const int last = int(min(d.M - 1 - row0, int64_t(kRows - 1)));
+        crow = row0 * KK;
+#pragma unroll
+        for (int q = 0; q < kCopies; q++) {
+            const int row = q * (64 / PG) + lane / PG, gr = (lane % PG) ^ swizzle(row);
+            src[q] = uint32_t(min(row, last) * int(KK) + min(4 * gr, tq - 4)) * 4u;
+        }
+    };
+    sources();
+    auto copy_t = [&]() {
+        const float* base = g.U + int64_t(ctu) * d.te_u + crow + int64_t(w + 4 * ci) * tq;
+        const uint32_t st = ring_lds + cstage * kStage;
+#pragma unroll
+        for (int q = 0; q < kCopies; q++) lds_copy16<true>(st + q * 1024, base, src[q]);
+        cstage = cstage == kRing - 1 ? 0 : cstage + 1;
+        if (++ci < ns) return;
+        if (cx + 1 >= i1) {
+            ci = ns - 1;  // past the end: the last chunk again, never read
+            return;
+        }
+        ci = 0;
+        cx++;
+        if (++ct == g.nt) {
+            ct = 0;
+            cblk++;
+            sources();
+        }
+        ctu = g.tu[ct];
+    };
+    // ---- Q and P rows of triple t, column block rb, into buffer x & 1
+    auto copy_qp = [&](int32_t t, int rb, int64_t x) {
+        const int64_t r = min(rb * kCols + lane, d.R - 1);
+        const float* Qt = g.Q + int64_t(g.tq[t]) * d.te_q;
+        const float* Pt = g.P + int64_t(g.tp[t]) * d.te_p;
+        const uint32_t to = qp_lds + uint32_t(x & 1) * qp_bytes;
+        for (int row = w; row < tq; row += 4) lds_copy4(to + row * 256, Qt + row * d.q_sq, uint32_t(r * d.q_sr) * 4u);
+        for (int row = w; row < tp; row += 4)
+            lds_copy4(to + (tq + row) * 256, Pt + row * d.p_sp, uint32_t(r * d.p_sr) * 4u);
+    };
+    copy_qp(ct, cblk % d.rblocks, i0);
+    int rstage = 0;  // the stage whose chunk is being used
+    float mx = 0.f;
+    Split8 fa[2];
+    const int rsw = swizzle(c);
+    auto read_t = [&](int stage, int s, float (&v)[8]) {
+        const char* row = ring + stage * kStage + c * (PG * 16);
+#pragma unroll
+        for (int i = 0; i < 2; i++) {
+            const float4 x = *reinterpret_cast<const float4*>(row + (((4 * s + 2 * half + i) ^ rsw) << 4));
+            v[4 * i] = x.x, v[4 * i + 1] = x.y, v[4 * i + 2] = x.z, v[4 * i + 3] = x.w;
+        }
+        if (!FULL && s == KS - 1) {
+#pragma unroll
+            for (int j = 0; j < 8; j++) v[j] = 16 * s + 8 * half + j < tq ? v[j] : 0.f;
+        }
+    };
+    if (ns > 0) {
+#pragma unroll
+        for (int q = 0; q < kRing; q++) copy_t();
+        lds_copy_wait<2 * kCopies>();  // the Q and P rows and the first chunk
+        float v[8];
+        read_t(0, 0, v);
+#pragma unroll
+        for (int i = 0; i < 4; i++) fa[0].set(i, v[2 * i], v[2 * i + 1], mx);
+    } else {
+        lds_copy_wait<0>();
+    }
+
+    floatx16 acc[2], y[2][2];
+    auto clear = [](floatx16& v) {
+#pragma unroll
+        for (int r = 0; r < 16; r++) v[r] = 0.f;
+    };
+    auto triple = [&](int64_t x, int32_t t, int rb) {
+        __syncthreads();  // Q and P are there; those of the triple before are done with
+        const char* buf = qp + (x & 1) * qp_bytes;
+        if (x + 1 < i1) {
+            const bool wrap = t + 1 == g.nt;
+            copy_qp(wrap ? 0 : t + 1, wrap ? (rb + 1 == d.rblocks ? 0 : rb + 1) : rb, x + 1);
+        }
+        Split8 fq[KS][2];
+#pragma unroll
+        for (int s = 0; s < KS; s++)
+#pragma unroll
+            for (int j = 0; j < 2; j++) {
+                float v[8];
+#pragma unroll
+                for (int e = 0; e < 8; e++) {
+                    const int k = 16 * s + 8 * half + e;
+                    v[e] = *reinterpret_cast<const float*>(buf + k * 256 + (32 * j + c) * 4);
+                    if (!FULL && s == KS - 1) v[e] = k < tq ? v[e] : 0.f;
+                }
+#pragma unroll
+                for (int i = 0; i < 4; i++) fq[s][j].set(i, v[2 * i], v[2 * i + 1], mx);
+            }
+        float pv[2][2] = {};  // [parity of the step][column tile]
+#pragma unroll
+        for (int a = 0; a < 2; a++)
+#pragma unroll
+            for (int j = 0; j < 2; j++) clear(y[a][j]);
+        // one p': y[A] = its product, acc += P y of the p' before (y[1 - A])
+        auto step = [&](auto parity, int i) {
+            constexpr int A = decltype(parity)::value;
+#pragma unroll
+            for (int j = 0; j < 2; j++)
+                pv[A][j] = *reinterpret_cast<const float*>(buf + (tq + w + 4 * i) * 256 + (32 * j + c) * 4);
+            asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(mx) : "v"(pv[A][0]), "v"(pv[A][1]));
+#pragma unroll
+            for (int s = 0; s < KS; s++) {
+                float v[8];
+                if (s + 1 < KS) {
+                    read_t(rstage, s + 1, v);
+                } else {
+                    // this chunk's values are all read: refill its stage, go on to the next
+                    copy_t();
+                    lds_copy_wait<2 * kCopies>();
+                    rstage = rstage == kRing - 1 ? 0 : rstage + 1;
+                    read_t(rstage, 0, v);
+                }
+                const Split8 a[1] = {fa[s & 1]};
+                floatx16 z[1][2];
+#pragma unroll
+                for (int j = 0; j < 2; j++) {
+                    if (s == 0) clear(z[0][j]);
+                    else z[0][j] = y[A][j];
+                }
+                Split8 nx;
+                constexpr int kSteps = kSplitSteps<1, 2>;  // 12
+#pragma unroll
+                for (int m = 0; m < kSteps; m++) {
+                    split_mma_step(m, z, a, fq[s]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    // scale-adds of the p' before: 16 per column tile, over the first and the last step
+                    if (s == 0 || s == KS - 1) {
+#pragma unroll
+                        for (int j = 0; j < 2; j++) {
+                            if (KS > 1 && j != (s == 0 ? 0 : 1)) continue;
+                            const int r0 = m * 16 / kSteps, r1 = (m + 1) * 16 / kSteps;
+#pragma unroll
+                            for (int r = r0; r < r1; r++) acc[j][r] = fmaf(pv[1 - A][j], y[1 - A][j][r], acc[j][r]);
+                        }
+                    }
+                    if (m >= 4 && m % 2 == 0) nx.set((m - 4) / 2, v[m - 4], v[m - 3], mx);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                fa[(s + 1) & 1] = nx;
+                y[A][0] = z[0][0];
+                y[A][1] = z[0][1];
+            }
+            if (KS % 2) fa[0] = fa[1];
+        };
+        for (int i = 0; i < ns; i += 2) {
+            step(std::integral_constant<int, 0>{}, i);
+            if (i + 1 < ns) step(std::integral_constant<int, 1>{}, i + 1);
+        }
+        // the last p' of the triple
+#pragma unroll
+        for (int j = 0; j < 2; j++) {
+            if (ns & 1) acc[j] += pv[0][j] * y[0][j];
+            else acc[j] += pv[1][j] * y[1][j];
+        }
+        if (ns < 2) lds_copy_wait<0>();  // (longer: the ring's waits covered the Q and P copies)
+    };
+    // the same sums on the fp32 MFMAs, straight from memory, for pieces that
+    // the split does not hold
+    auto triple_fp32 = [&](int32_t t, int64_t row0, int col0) {
+        const float* Tt = g.U + int64_t(g.tu[t]) * d.te_u + min(row0 + c, d.M - 1) * KK;
+        const float* Pt = g.P + int64_t(g.tp[t]) * d.te_p;
+        const float* Qt = g.Q + int64_t(g.tq[t]) * d.te_q;
+        const int64_t r[2] = {min(col0 + c, d.R - 1), min(col0 + 32 + c, d.R - 1)};
+        for (int pp = w; pp < tp; pp += 4) {
+            floatx16 z[2];
+            clear(z[0]);
+            clear(z[1]);
+            for (int k0 = 0; k0 < tq; k0 += 16)
+#pragma unroll
+                for (int e = 0; e < 8; e++) {
+                    const int k = k0 + 8 * half + e, kc = min(k, tq - 1);
+                    const float a = k < tq ? Tt[pp * tq + kc] : 0.f;
+#pragma unroll
+                    for (int j = 0; j < 2; j++) {
+                        const float b = k < tq ? Qt[kc * d.q_sq + r[j] * d.q_sr] : 0.f;
+                        z[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, z[j], 0, 0, 0);
+                    }
+                }
+#pragma unroll
+            for (int j = 0; j < 2; j++) acc[j] += Pt[pp * d.p_sp + r[j] * d.p_sr] * z[j];
+        }
+    };
+    // Walk the range as pieces, each the part of one (segment, block) in it.
+    for (int64_t i = i0; i < i1;) {
         const int64_t blk = i / g.nt;
         const int32_t t = int32_t(i - blk * g.nt);
         const int32_t q = g.seg_of[t + 1] - 1;
@@ -267,275 +500,77 @@ __device__ inline void for_each_piece(const F3Args& g, Begin begin, Triple tripl
         const int64_t pend = min(i1, blk * g.nt + s1);
         const bool before = s0 < t, cont = blk * g.nt + s1 > i1;
         const int mb = int(blk / d.rblocks), rb = int(blk % d.rblocks);
-        begin(mb, rb);
-        const int32_t t_end = t + int32_t(pend - i);
-        for (int32_t tt = t; tt < t_end; tt++) triple(tt, tt + 1 < t_end ? tt + 1 : -1);
         Dest dst;
-        dst.row0 = int64_t(mb) * g.brows;
+        dst.row0 = int64_t(mb) * kRows;
         dst.col0 = rb * kCols;
         dst.slot = before || cont;
         dst.base = !dst.slot ? g.W + int64_t(q) * d.te_w
-                             : g.part + (2 * b + (before ? 0 : 1)) * int64_t(g.brows) * kCols;
-        end(dst);
+                             : g.part + (2 * int64_t(blockIdx.x) + (before ? 0 : 1)) * int64_t(kRows) * kCols;
+        clear(acc[0]);
+        clear(acc[1]);
+        for (int64_t x = i; x < pend; x++) triple(x, t + int32_t(x - i), rb);
+        // sum over the wavefronts, in the buffer of the piece's last Q and P:
+        // wavefront w keeps registers 4 w .. 4 w + 3 of both column tiles
+        float* red = reinterpret_cast<float*>(qp + ((pend - 1) & 1) * qp_bytes);
+        float res[2][4];
+        auto sum = [&]() {
+#pragma unroll
+            for (int j = 0; j < 2; j++) {
+                __syncthreads();
+#pragma unroll
+                for (int r = 0; r < 16; r++) red[(w * 16 + r) * 64 + lane] = acc[j][r];
+                __syncthreads();
+#pragma unroll
+                for (int r = 0; r < 4; r++) {
+                    float v = 0.f;
+#pragma unroll
+                    for (int u = 0; u < 4; u++) v += red[(u * 16 + 4 * w + r) * 64 + lane];
+                    res[j][r] = v;
+                }
+            }
+        };
+        sum();
+        auto row_of = [&](int r) { return 8 * w + 4 * half + r; };
+        SplitCheck check;
+#pragma unroll
+        for (int j = 0; j < 2; j++)
+#pragma unroll
+            for (int r = 0; r < 4; r++)
+                if (dst.row0 + row_of(r) < d.M && dst.col0 + 32 * j + c < d.R) check.add(res[j][r]);
+        // (three factors: inputs up to 2^16 keep a lost part, times the other
+        // two, below 2^-94)
+        bool redo = __ballot(check.bad(mx, 0x1p16f)) != 0;
+        __syncthreads();
+        if (lane == 0) red[w] = redo ? 1.f : 0.f;
+        __syncthreads();
+        redo = red[0] + red[1] + red[2] + red[3] != 0.f;
+        if (redo) {
+            clear(acc[0]);
+            clear(acc[1]);
+            for (int64_t x = i; x < pend; x++) triple_fp32(t + int32_t(x - i), dst.row0, dst.col0);
+            sum();
+        }
+#pragma unroll
+        for (int j = 0; j < 2; j++)
+#pragma unroll
+            for (int r = 0; r < 4; r++) dst.put(d, row_of(r), 32 * j + c, res[j][r]);
         i = pend;
     }
+    lds_copy_wait<0>();  // copies past the end must land before the LDS is given away
 }
 
-// T chunk loads: 32 rows x kChunk elements, 4 float4 per thread.
-struct ChunkLoader {
-    float4 pre[4];
-    __device__ void load(const F3Desc& d, const float* Tt, int64_t row0, int64_t KK, int c) {
-        const int tid = threadIdx.x;
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            const int idx = tid + kThreads * i, row = idx >> 5, c4 = idx & 31;
-            const int64_t kk = int64_t(c) * kChunk + 4 * c4;
-            const int64_t m = row0 + row;
-            pre[i] = (m < d.M && kk < KK) ? *reinterpret_cast<const float4*>(Tt + m * KK + kk)
-                                          : float4{0.f, 0.f, 0.f, 0.f};
-        }
+using GemmFn = void (*)(F3Args);
+GemmFn gemm_kernel(const F3Desc& d) {
+    switch ((d.tq + 15) / 16 * 2 + (d.tq % 16 == 0)) {
+        case 2: return k3_gemm<1, false>;
+        case 3: return k3_gemm<1, true>;
+        case 4: return k3_gemm<2, false>;
+        case 5: return k3_gemm<2, true>;
+        case 6: return k3_gemm<3, false>;
+        case 7: return k3_gemm<3, true>;
+        case 8: return k3_gemm<4, false>;
+        default: return k3_gemm<4, true>;
     }
-    __device__ void store(float* st) const {
-        const int tid = threadIdx.x;
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            const int idx = tid + kThreads * i, row = idx >> 5, c4 = idx & 31;
-            *reinterpret_cast<float4*>(st + row * kPitchT + 4 * c4) = pre[i];
-        }
-    }
-};
-
-// Stage the block's columns of the triple's P tile ([tp][kCols]) and Q tile
-// (transposed, [kCols][qpitch]) in LDS.
-__device__ inline void stage_pq(const F3Desc& d, const float* Pt, const float* Qt, int col0, int tq, int qpitch,
-                                float* sP, float* sQ) {
-    const int tid = threadIdx.x;
-    for (int e = tid; e < d.tp * kCols; e += kThreads) {
-        const int pp = e / kCols, c = e % kCols, r = col0 + c;
-        sP[e] = r < d.R ? Pt[pp * d.p_sp + int64_t(r) * d.p_sr] : 0.f;
-    }
-    for (int e = tid; e < tq * kCols; e += kThreads) {
-        const int qq = e / kCols, c = e % kCols, r = col0 + c;
-        sQ[c * qpitch + qq] = r < d.R ? Qt[qq * d.q_sq + int64_t(r) * d.q_sr] : 0.f;
-    }
-}
-
-// The P and Q slices for k3_gemm_q, both row-major [rows][kCols] (Q not
-// transposed).  When the block's columns all lie inside R, straight from
-// memory into LDS (global_load_lds_dword: lane l of a wavefront lands at the
-// instruction's LDS address + 4 l), every load issued before the wait at the
-// next barrier and no registers held; otherwise through registers as above.
-__device__ inline void stage_pq_rows(const F3Desc& d, const float* Pt, const float* Qt, int col0, int tq, float* sP,
-                                     float* sQ) {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    if (col0 + kCols <= d.R) {
-        const int64_t r = col0 + lane;
-        for (int row = w; row < d.tp; row += kThreads / 64)
-            __builtin_amdgcn_global_load_lds(
-                (const __attribute__((address_space(1))) void*)(Pt + row * d.p_sp + r * d.p_sr),
-                (__attribute__((address_space(3))) void*)(sP + row * kCols), 4, 0, 0);
-        for (int row = w; row < tq; row += kThreads / 64)
-            __builtin_amdgcn_global_load_lds(
-                (const __attribute__((address_space(1))) void*)(Qt + row * d.q_sq + r * d.q_sr),
-                (__attribute__((address_space(3))) void*)(sQ + row * kCols), 4, 0, 0);
-        return;
-    }
-    const int tid = threadIdx.x;
-    for (int e = tid; e < d.tp * kCols; e += kThreads) {
-        const int r = col0 + e % kCols;
-        sP[e] = r < d.R ? Pt[(e / kCols) * d.p_sp + int64_t(r) * d.p_sr] : 0.f;
-    }
-    for (int e = tid; e < tq * kCols; e += kThreads) {
-        const int r = col0 + e % kCols;
-        sQ[e] = r < d.R ? Qt[(e / kCols) * d.q_sq + int64_t(r) * d.q_sr] : 0.f;
-    }
-}
-
-// Any tq (a multiple of 4).  Dynamic LDS: T stages [2][kRows][kPitchT], P
-// slice [tp][kCols], Q slice transposed [kCols][tq + 4] (floats).  Waves:
-// rows [16 mh, +16) and columns [32 rh, +32) of the block; the B operand of
-// every MFMA is P[p', r] * Q[q', r] formed in registers.
-__global__ __launch_bounds__(kThreads) void k3_gemm(F3Args g) {
-    extern __shared__ float lds[];
-    const F3Desc& d = g.d;
-    float* sT = lds;
-    float* sP = lds + 2 * kRows * kPitchT;
-    const int qpitch = d.tq + 4;
-    float* sQ = sP + d.tp * kCols;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int mh = w & 1, rh = w >> 1;
-    const int n = lane & 15, gq = lane >> 4;
-    const int64_t KK = int64_t(d.tp) * d.tq;
-    const int nchunks = int((KK + kChunk - 1) / kChunk);
-    floatx4 acc[2][2];
-    int64_t row0 = 0;
-    int col0 = 0;
-    ChunkLoader ld;
-    auto begin = [&](int mb, int rb) {
-        row0 = int64_t(mb) * kRows;
-        col0 = rb * kCols;
-#pragma unroll
-        for (int t = 0; t < 2; t++)
-#pragma unroll
-            for (int e = 0; e < 2; e++) acc[t][e] = floatx4{0.f, 0.f, 0.f, 0.f};
-    };
-    auto triple = [&](int32_t t, int32_t) {
-        const float* Tt = g.U + int64_t(g.tu[t]) * d.te_u;
-        __syncthreads();  // the previous triple is done with sP, sQ and both T stages
-        stage_pq(d, g.P + int64_t(g.tp[t]) * d.te_p, g.Q + int64_t(g.tq[t]) * d.te_q, col0, d.tq, qpitch, sP, sQ);
-        ld.load(d, Tt, row0, KK, 0);
-        for (int c = 0; c < nchunks; c++) {
-            float* st = sT + (c & 1) * kRows * kPitchT;
-            ld.store(st);
-            __syncthreads();
-            if (c + 1 < nchunks) ld.load(d, Tt, row0, KK, c + 1);
-            // this lane's contracted index at the chunk start, as (p', q')
-            int64_t kk0 = int64_t(c) * kChunk + 4 * gq;
-            int pp = int(kk0 / d.tq), qq = int(kk0 % d.tq);
-            const float* arow = st + (16 * mh + n) * kPitchT + 4 * gq;
-#pragma unroll 2
-            for (int kq = 0; kq < kChunk / 16; kq++) {
-                const float4 a4 = *reinterpret_cast<const float4*>(arow + 16 * kq);
-                const bool ok = kk0 < KK;
-                const int ppc = ok ? pp : 0, qqc = ok ? qq : 0;
-#pragma unroll
-                for (int tt = 0; tt < 2; tt++) {
-                    const int cl = 32 * rh + 16 * tt + n;
-                    const float pv = ok ? sP[ppc * kCols + cl] : 0.f;
-                    const float4 q4 = *reinterpret_cast<const float4*>(sQ + cl * qpitch + qqc);
-                    acc[tt][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4.x, pv * q4.x, acc[tt][0], 0, 0, 0);
-                    acc[tt][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4.y, pv * q4.y, acc[tt][1], 0, 0, 0);
-                    acc[tt][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4.z, pv * q4.z, acc[tt][0], 0, 0, 0);
-                    acc[tt][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4.w, pv * q4.w, acc[tt][1], 0, 0, 0);
-                }
-                kk0 += 16;
-                qq += 16;
-                while (qq >= d.tq) {
-                    qq -= d.tq;
-                    pp++;
-                }
-            }
-        }
-    };
-    auto end = [&](const Dest& dst) {
-        // lane holds rows 4 gq + i, column n of each 16 x 16 tile
-#pragma unroll
-        for (int tt = 0; tt < 2; tt++) {
-            const floatx4 v = acc[tt][0] + acc[tt][1];
-#pragma unroll
-            for (int i = 0; i < 4; i++) dst.put(d, 16 * mh + 4 * gq + i, 32 * rh + 16 * tt + n, v[i]);
-        }
-    };
-    for_each_piece(g, begin, triple, end);
-}
-
-// tq = TQ in {16, 32, 64}, ordered the other way round: for every p' the
-// MFMAs contract over q' only, Y[m, r] = sum_q' T[m, p', q'] Q[q', r], and
-// the result is scaled by P[p', r] and added to the accumulator (acc +=
-// P[p', r] * Y[m, r], one fused multiply-add per element and p').  The B
-// operand of every MFMA is then a plain Q element, held in registers for the
-// whole triple (lane group g of the 16x16x4 MFMA takes q' = g * TQ/4 + s for
-// step s, so a lane's A values are contiguous in the staged T row and come
-// in 16-byte LDS reads), and the scale-add of p' - 1 is issued after the
-// MFMAs of p' so that it does not wait for them.  The first T chunk of the
-// piece's next triple is loaded during the last chunk of the current one.
-template <int TQ>
-__global__ __launch_bounds__(kThreads, 3) void k3_gemm_q(F3Args g) {
-    constexpr int kS = TQ / 4;           // MFMA steps per p'
-    constexpr int kPpc = kChunk / TQ;    // p' rows per staged chunk
-    static_assert(kS % 4 == 0 && kChunk % TQ == 0, "TQ must be 16, 32 or 64");
-    extern __shared__ float lds[];
-    const F3Desc& d = g.d;
-    float* sT = lds;
-    float* sP = lds + 2 * kRows * kPitchT;
-    constexpr int qpitch = TQ + 4;
-    float* sQ = sP + d.tp * kCols;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int mh = w & 1, rh = w >> 1;
-    const int n = lane & 15, gq = lane >> 4;
-    const int64_t KK = int64_t(d.tp) * TQ;
-    const int nchunks = int((KK + kChunk - 1) / kChunk);
-    const int cl0 = 32 * rh + n, cl1 = cl0 + 16;  // this lane's two columns in the block
-    const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
-    floatx4 acc[2], yprev[2];
-    float pvprev[2];
-    int64_t row0 = 0;
-    int col0 = 0;
-    bool have_next = false;  // the first chunk of the next triple is in ld
-    ChunkLoader ld;
-    auto begin = [&](int mb, int rb) {
-        row0 = int64_t(mb) * kRows;
-        col0 = rb * kCols;
-        have_next = false;
-#pragma unroll
-        for (int t = 0; t < 2; t++) {
-            acc[t] = yprev[t] = zero;
-            pvprev[t] = 0.f;
-        }
-    };
-    auto triple = [&](int32_t t, int32_t t_next) {
-        const float* Tt = g.U + int64_t(g.tu[t]) * d.te_u;
-        __syncthreads();  // the previous triple is done with sP, sQ and both T stages
-        stage_pq_rows(d, g.P + int64_t(g.tp[t]) * d.te_p, g.Q + int64_t(g.tq[t]) * d.te_q, col0, TQ, sP, sQ);
-        if (!have_next) ld.load(d, Tt, row0, KK, 0);
-        have_next = false;
-        float qreg[2][kS];
-        for (int c = 0; c < nchunks; c++) {
-            float* st = sT + (c & 1) * kRows * kPitchT;
-            ld.store(st);
-            __syncthreads();
-            if (c + 1 < nchunks) {
-                ld.load(d, Tt, row0, KK, c + 1);
-            } else if (t_next >= 0) {
-                ld.load(d, g.U + int64_t(g.tu[t_next]) * d.te_u, row0, KK, 0);
-                have_next = true;
-            }
-            if (c == 0) {
-                // this lane's Q elements for the whole triple: q' = gq * kS + j
-#pragma unroll
-                for (int j = 0; j < kS; j++) {
-                    qreg[0][j] = sQ[(gq * kS + j) * kCols + cl0];
-                    qreg[1][j] = sQ[(gq * kS + j) * kCols + cl1];
-                }
-            }
-            const float* arow = st + (16 * mh + n) * kPitchT + gq * kS;
-#pragma unroll
-            for (int pl = 0; pl < kPpc; pl++) {
-                const int pg = c * kPpc + pl;  // p' of this row of the chunk
-                float a[kS];
-#pragma unroll
-                for (int j = 0; j < kS; j += 4) {
-                    const float4 v = *reinterpret_cast<const float4*>(arow + pl * TQ + j);
-                    a[j] = v.x, a[j + 1] = v.y, a[j + 2] = v.z, a[j + 3] = v.w;
-                }
-                const int pc = min(pg, d.tp - 1);
-                const float p0 = sP[pc * kCols + cl0], p1 = sP[pc * kCols + cl1];
-                floatx4 y0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[0], qreg[0][0], zero, 0, 0, 0);
-                floatx4 y1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[0], qreg[1][0], zero, 0, 0, 0);
-#pragma unroll
-                for (int j = 1; j < kS; j++) {
-                    y0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], qreg[0][j], y0, 0, 0, 0);
-                    y1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], qreg[1][j], y1, 0, 0, 0);
-                }
-                // scale-add of the previous p' while these MFMAs run
-                acc[0] += pvprev[0] * yprev[0];
-                acc[1] += pvprev[1] * yprev[1];
-                yprev[0] = y0;
-                yprev[1] = y1;
-                pvprev[0] = pg < d.tp ? p0 : 0.f;
-                pvprev[1] = pg < d.tp ? p1 : 0.f;
-            }
-        }
-    };
-    auto end = [&](const Dest& dst) {
-        acc[0] += pvprev[0] * yprev[0];
-        acc[1] += pvprev[1] * yprev[1];
-#pragma unroll
-        for (int tt = 0; tt < 2; tt++)
-#pragma unroll
-            for (int i = 0; i < 4; i++) dst.put(d, 16 * mh + 4 * gq + i, 32 * rh + 16 * tt + n, acc[tt][i]);
-    };
-    for_each_piece(g, begin, triple, end);
 }
 
 // Sum the slots of every split (segment, block): workgroup b - 1 of this
@@ -890,10 +925,6 @@ F3Layout f3_layout(const F3Desc& d, int64_t n_u) {
     return L;
 }
 
-size_t gemm_lds_bytes(const F3Desc& d) {
-    return sizeof(float) * (size_t(2) * kRows * kPitchT + size_t(d.tp) * kCols + size_t(kCols) * (d.tq + 4));
-}
-
 }  // namespace
 
 }  // namespace tre
@@ -1115,10 +1146,8 @@ tre_status tre_execute3(const char* einsum, const char* upper, const int64_t* ex
         }
         tm.mark(s);
     } else {
-        const void* fn = d.tq == 16   ? reinterpret_cast<const void*>(&k3_gemm_q<16>)
-                         : d.tq == 32 ? reinterpret_cast<const void*>(&k3_gemm_q<32>)
-                         : d.tq == 64 ? reinterpret_cast<const void*>(&k3_gemm_q<64>)
-                                      : reinterpret_cast<const void*>(&k3_gemm);
+        const GemmFn kernel = gemm_kernel(d);
+        const void* fn = reinterpret_cast<const void*>(kernel);
         const size_t lds = gemm_lds_bytes(d);
         F3Args g{};
         if (nw > 0) {
@@ -1150,11 +1179,7 @@ tre_status tre_execute3(const char* einsum, const char* upper, const int64_t* ex
             g.d = d;
             const dim3 grid{unsigned(n_wg)};
             t_kernel_events = kep;
-            e = launch_k(d.tq == 16   ? k3_gemm_q<16>
-                         : d.tq == 32 ? k3_gemm_q<32>
-                         : d.tq == 64 ? k3_gemm_q<64>
-                                      : k3_gemm,
-                         grid, dim3(kThreads), lds, s, g);
+            e = launch_k(kernel, grid, dim3(kThreads), lds, s, g);
             t_kernel_events = nullptr;
             if (e != hipSuccess) return dev_fail(e, "contract");
         }

@@ -114,9 +114,9 @@ struct SplitCheck {
         top = max(top, t);
         low = min(low, t - 1);  // zero wraps to the largest
     }
-    __device__ bool bad(float max_input) const {
+    __device__ bool bad(float max_input, float limit = kSplitMaxInput) const {
         constexpr uint32_t kInf2 = 0xff000000u, kMin2 = uint32_t(127 - 50) << 24;
-        return top >= kInf2 || low < kMin2 - 1 || !(max_input <= kSplitMaxInput);
+        return top >= kInf2 || low < kMin2 - 1 || !(max_input <= limit);
     }
 };
 

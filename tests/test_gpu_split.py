@@ -103,3 +103,52 @@ def test_split_against_float64(name, kind):
     assert np.max(np.abs(got[fin] - ref[fin]) / mag[fin]) <= 16 * 2.0 ** -24
     if kind == "normal":
         assert np.linalg.norm(got - ref) / np.linalg.norm(ref) <= 1e-6
+
+
+def three_way(tp, tq, m, r, n_u, rng, kind="normal"):
+    """A[i, r] = sum_jk T[i, j, k] B[j, r] C[k, r] on n_u random tuples of a
+    5 x 4 x 4 key grid, with the float64 value and magnitude per output tuple."""
+    import torch
+
+    ext = {"i": 5 * m, "j": 4 * tp, "k": 4 * tq, "r": r}
+    til = {"i": m, "j": tp, "k": tq}
+    ids = np.sort(rng.choice(80, size=n_u, replace=False))
+    tk = np.stack([ids // 16, ids // 4 % 4, ids % 4], 1).astype(np.int32)
+    t, b = values(kind, rng, [(n_u, m, tp, tq), (4, tp, r)])
+    c = rng.standard_normal((4, tq, r)).astype(np.float32)
+    if kind == "largest":  # the products with C are summed first, in fp32: 3.4e38 x 4 x 1e-3 fits
+        c *= np.float32(1e-3)
+    rows, at = np.unique(tk[:, 0], return_inverse=True)
+    ref, mag = np.zeros((len(rows), m, r)), np.zeros((len(rows), m, r))
+    with np.errstate(invalid="ignore", over="ignore"):
+        for s in range(n_u):
+            args = (t[s].astype(np.float64), b[tk[s, 1]].astype(np.float64), c[tk[s, 2]].astype(np.float64))
+            ref[at[s]] += np.einsum("ijk,jr,kr->ir", *args)
+            mag[at[s]] += np.einsum("ijk,jr,kr->ir", *(np.abs(x) for x in args))
+    k1 = torch.arange(4, dtype=torch.int32, device="cuda").reshape(4, 1)
+    wk, wt, nt = tre.execute3("ijk,jr,kr->ir", "ijk", ext, til, torch.from_numpy(tk).cuda(),
+                              torch.from_numpy(t.reshape(n_u, -1)).cuda(), k1, torch.from_numpy(b.reshape(4, -1)).cuda(),
+                              k1.clone(), torch.from_numpy(c.reshape(4, -1)).cuda())
+    assert nt == n_u and np.array_equal(wk.cpu().numpy()[:, 0], rows)
+    return wt.cpu().numpy().reshape(ref.shape), ref, mag
+
+
+@pytest.mark.parametrize("tq", [4, 12, 16, 20, 32, 36, 48, 52, 64])
+def test_three_operands_against_float64(tq):
+    """Every count of 16-wide steps, whole and partial, with 1 to 64 rows of p
+    (fewer than the wavefronts that share them too), partial row and column blocks."""
+    rng = np.random.default_rng(tq)
+    for tp, m, r, n_u in ((1, 5, 7, 40), (3, 32, 64, 61), (8, 33, 65, 17), (32, 40, 70, 9), (64, 16, 40, 30)):
+        got, ref, mag = three_way(tp, tq, m, r, n_u, rng)
+        # (tp tq n products summed in fp32, in practice well below sqrt(n) 2^-24)
+        assert np.max(np.abs(got - ref) / mag) <= 32 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("kind", ["inf", "nan", "largest", "tiny", "tiny_times_huge"])
+def test_three_operands_split(kind):
+    got, ref, mag = three_way(8, 32, 32, 64, 20, np.random.default_rng(3), kind)
+    fin = np.isfinite(ref)
+    # (infinities: the fp32 sums may meet +inf - inf where float64's do, and only there)
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    assert np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
+    assert np.max(np.abs(got[fin] - ref[fin]) / mag[fin]) <= 32 * 2.0 ** -24
