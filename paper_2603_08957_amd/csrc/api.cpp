@@ -193,14 +193,9 @@ tre_status join_enqueue(tre_plan_t plan, const int32_t* u_keys, int64_t n_u, con
     out->internal[4] = uint64_t(max_pairs);
     const Layout L = make_layout(p, n_u, n_v, max_pairs);
     char* w = reinterpret_cast<char*>(ws);
-    hipError_t e = launch_fill_zero(w + L.hdr, sizeof(WsHeader), s);
-    if (e != hipSuccess) return dev_fail(e, "header");
+    hipError_t e;
+    const bool validate = p.opt.validate_keys != 0;
     WsHeader* hdr = reinterpret_cast<WsHeader*>(w + L.hdr);
-    if (p.opt.validate_keys) {
-        const ValJob jobs[2] = {{u_keys, n_u, p.nk[0], p.radix[0], &hdr->err_u, n_u_dev},
-                                {v_keys, n_v, p.nk[1], p.radix[1], &hdr->err_v, nullptr}};
-        if ((e = launch_validate(jobs, 2, s)) != hipSuccess) return dev_fail(e, "validate");
-    }
     if (n_u > 0 && n_v == 1 && keyed_by_u(p)) {
         // one pair and one group per U tuple: nothing to count
         if (n_u > max_pairs) {
@@ -208,7 +203,7 @@ tre_status join_enqueue(tre_plan_t plan, const int32_t* u_keys, int64_t n_u, con
             set_error("tre_join: workspace too small for the matched pairs (see n_pairs)");
             return TRE_E_WORKSPACE;
         }
-        if ((e = launch_keyed_by_u(p, L, w, u_keys, s, n_u_dev)) != hipSuccess) return dev_fail(e, "join");
+        if ((e = launch_keyed_by_u(p, L, w, u_keys, s, n_u_dev, validate)) != hipSuccess) return dev_fail(e, "join");
         st->cap = n_u;
         st->counts_known = true;
         st->path = 4;
@@ -231,7 +226,18 @@ tre_status join_enqueue(tre_plan_t plan, const int32_t* u_keys, int64_t n_u, con
     st->cap = (n_u > 0 && n_v > 0) ? std::max<int64_t>(cap, 0) : 0;
     st->small = n_u > 0 && n_v > 0 && small_join_ok(p, n_u, n_v, cap);
     if (st->small) {
-        if ((e = launch_join_small(p, L, w, u_keys, v_keys, cap, s)) != hipSuccess) return dev_fail(e, "join");
+        if ((e = launch_join_small(p, L, w, u_keys, v_keys, cap, s, validate)) != hipSuccess) return dev_fail(e, "join");
+    } else if (vd || ud) {
+        if ((e = launch_group(p, L, w, u_keys, v_keys, cap, s, validate)) != hipSuccess) return dev_fail(e, "group");
+    } else if ((e = launch_fill_zero(hdr, sizeof(WsHeader), s)) != hipSuccess) {
+        return dev_fail(e, "header");
+    } else if (validate) {
+        const ValJob jobs[2] = {{u_keys, n_u, p.nk[0], p.radix[0], &hdr->err_u, n_u_dev},
+                                {v_keys, n_v, p.nk[1], p.radix[1], &hdr->err_v, nullptr}};
+        if ((e = launch_validate(jobs, 2, s)) != hipSuccess) return dev_fail(e, "validate");
+    }
+    if (st->small || vd || ud) {
+        // joined whole, with the key checks
     } else if (n_u > 0 && n_v > 0 && max_pairs > 0) {
         if ((e = launch_join(p, L, w, u_keys, v_keys, s, 0)) != hipSuccess) return dev_fail(e, "join");
         if ((e = launch_group(p, L, w, u_keys, v_keys, cap, s)) != hipSuccess) return dev_fail(e, "group");
@@ -288,19 +294,27 @@ void join_timing(tre_timing* timing, int32_t path) {
     timing->join_path = path;
 }
 
-// tre_contract's launches, for the join's counts n_pairs and n_w.  With
+// tre_contract's launches, for the join's counts n_pairs and n_w, and the
+// counts of an asynchronous call (counts not null).  With
 // `dev` those are upper bounds and every kernel reads the join's counts from
 // the workspace header (the caller has checked that the bounds need no U
 // ranges and take a one-workgroup unit table or one unit per key).
 tre_status contract_enqueue(tre_plan_t plan, const tre_join_result* jr, int64_t n_pairs, int64_t n_w,
                             const void* u_tiles, const void* v_tiles, int32_t* w_keys, void* w_out,
-                            int32_t* pairs_out, hipStream_t s, tre_timing* timing, bool dev = false) {
+                            int32_t* pairs_out, hipStream_t s, tre_timing* timing, bool dev = false,
+                            int64_t* counts = nullptr) {
     // W's element type is the plan's (fp32, or bf16 bits with w_bf16); the
     // kernels take the array as float* and store 16-bit elements through it
     // when the plan says bf16
     float* w_tiles = static_cast<float*>(w_out);
     const Plan& p = plan->p;
-    if (n_pairs == 0) return TRE_OK;
+    if (n_pairs == 0) {
+        if (!counts) return TRE_OK;
+        const Layout L = make_layout(p, jr->n_u, jr->n_v, int64_t(jr->internal[4]));
+        const hipError_t e = launch_write_outputs(p, L, reinterpret_cast<char*>(jr->internal[2]), nullptr, nullptr, 0, 0,
+                                                  s, true, counts);
+        return e == hipSuccess ? TRE_OK : dev_fail(e, "counts");
+    }
     if (!u_tiles || !v_tiles || !w_tiles || (p.nk[2] > 0 && !w_keys)) {
         set_error("tre_contract: null tile or key buffer");
         return TRE_E_ARG;
@@ -335,6 +349,9 @@ tre_status contract_enqueue(tre_plan_t plan, const tre_join_result* jr, int64_t 
         if ((e = launch_tables(p, reinterpret_cast<int32_t*>(w + L.tables), s)) != hipSuccess)
             return dev_fail(e, "tables");
         e = launch_range_units(p, L, w, n_w, jr->n_u, R, s);
+    } else if (one_pair_keys) {
+        // the join wrote the units
+        e = launch_tables(p, reinterpret_cast<int32_t*>(w + L.tables), s);
     } else {
         e = launch_units(p, L, w, n_pairs, n_w, p_unit, !pace, s, dev);
     }
@@ -360,7 +377,7 @@ tre_status contract_enqueue(tre_plan_t plan, const tre_join_result* jr, int64_t 
         const int64_t split_bound = R > 1 ? n_w : std::min<int64_t>(n_w, n_pairs / (p_unit + 1) + 1);
         if ((e = launch_reduce(p, L, w, w_tiles, split_bound, s)) != hipSuccess) return dev_fail(e, "reduce");
     }
-    if ((e = launch_write_outputs(p, L, w, w_keys, pairs_out, n_pairs, n_w, s, dev)) != hipSuccess)
+    if ((e = launch_write_outputs(p, L, w, w_keys, pairs_out, n_pairs, n_w, s, dev, counts)) != hipSuccess)
         return dev_fail(e, "outputs");
     tm.mark(s);
     if (timing) {
@@ -584,11 +601,8 @@ tre_status tre_execute_async(tre_plan_t plan, const int32_t* u_keys, int64_t n_u
     tm.mark(s);
     join_timing(timing, js.path);
     if ((st = contract_enqueue(plan, &jr, b.pairs, b.keys, u_tiles, v_tiles, w_keys, w_tiles, pairs_out, s, timing,
-                               true)) != TRE_OK)
+                               true, counts)) != TRE_OK)
         return st;
-    const Layout L = make_layout(p, n_u, n_v, max_pairs);
-    const hipError_t e = launch_counts_out(L, static_cast<char*>(ws), max_pairs, counts, s);
-    if (e != hipSuccess) return dev_fail(e, "counts");
     if (timing && !timing->deferred) {
         const float jm = tm.between(0, 1);
         timing->join_ms = jm;

@@ -31,8 +31,8 @@ __device__ inline float ld_f(const uint16_t* p) { return __uint_as_float(uint32_
 // ---------------------------------------------------------------- tables
 
 // off[t] < 0: the plan's contraction kernel does not read table t (the
-// GEMM class reads the W tables and, where it gathers its operands, theirs,
-// the vector class the E/K ones, the 128x128 path none), so it is not
+// GEMM class reads those of W and of its operands where their offsets are not
+// affine, the vector class the E/K ones, the 128x128 path none), so it is not
 // written.
 struct TableSet {
     Dims d[T_COUNT];
@@ -657,27 +657,44 @@ struct Unpack {
     int32_t bits[26];
 };
 
+// A call's output keys and pair list, and for an asynchronous one (counts not
+// null) its counts: [0] the pairs, [1] the output keys, [2] a tre_status (key
+// errors as on the host, pairs beyond the workspace's capacity), [3] zero.
 // (dn: the counts from the join's header, the host's being bounds)
-__global__ void k_write_keys(const uint64_t* __restrict__ seg_key, int64_t n_w, Unpack up, int32_t* __restrict__ out,
-                             const WsHeader* __restrict__ dn) {
-    const int64_t s = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (dn) n_w = min(n_w, dn->n_w);
-    if (s >= n_w) return;
-    uint64_t k = seg_key[s];
-    for (int c = up.n - 1; c >= 0; c--) {
-        const int b = up.bits[c];
-        out[s * up.n + c] = int32_t(b ? (k & ((uint64_t(1) << b) - 1)) : 0);
-        k = b < 64 ? (k >> b) : 0;
+__global__ void k_outputs(const uint64_t* __restrict__ seg_key, int64_t n_w, Unpack up, int32_t* __restrict__ w_keys,
+                          const int32_t* __restrict__ pu, const int32_t* __restrict__ pv, int64_t n_pairs,
+                          int32_t* __restrict__ pairs, const WsHeader* __restrict__ dn, int64_t max_pairs,
+                          int64_t* __restrict__ counts) {
+    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (counts && i == 0) {
+        auto key_status = [](int32_t f) {
+            return (f & 4) ? int64_t(TRE_E_KEYRANGE) : (f & 1) ? int64_t(TRE_E_UNSORTED) : (f & 2) ? int64_t(TRE_E_DUPKEY) : 0;
+        };
+        int64_t st = key_status(dn->err_u);
+        if (st == 0) st = key_status(dn->err_v);
+        const int64_t np = dn->n_pairs;
+        if (st == 0 && np > max_pairs) st = TRE_E_WORKSPACE;
+        counts[0] = np;
+        counts[1] = np > 0 ? dn->n_w : 0;
+        counts[2] = st;
+        counts[3] = 0;
     }
-}
-
-__global__ void k_write_pairs(const int32_t* __restrict__ pu, const int32_t* __restrict__ pv, int64_t n,
-                              int32_t* __restrict__ out, const WsHeader* __restrict__ dn) {
-    const int64_t p = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (dn) n = min(n, dn->n_pairs);
-    if (p >= n) return;
-    out[2 * p] = pu[p];
-    out[2 * p + 1] = pv[p];
+    if (dn) {
+        n_w = min(n_w, dn->n_w);
+        n_pairs = min(n_pairs, dn->n_pairs);
+    }
+    if (w_keys && i < n_w) {
+        uint64_t k = seg_key[i];
+        for (int c = up.n - 1; c >= 0; c--) {
+            const int b = up.bits[c];
+            w_keys[i * up.n + c] = int32_t(b ? (k & ((uint64_t(1) << b) - 1)) : 0);
+            k = b < 64 ? (k >> b) : 0;
+        }
+    }
+    if (pairs && i < n_pairs) {
+        pairs[2 * i] = pu[i];
+        pairs[2 * i + 1] = pv[i];
+    }
 }
 
 inline unsigned blocks_for(int64_t n) { return unsigned((n + kThreads - 1) / kThreads); }
@@ -691,7 +708,8 @@ bool table_used(const Plan& p, int t) {
     if (p.kclass == KC_VEC) return t >= T_EU;
     if (p.fast || t >= T_EU) return false;
     if (t == T_AM || t == T_AK || t == T_BN || t == T_BK) return p.tile_op[0].mode == TM_GATHER;
-    return true;
+    if (t == T_WM || t == T_WN) return !p.tile_w_affine;
+    return p.nB > 1;
 }
 
 // The tables the contraction reads (the others marked off = -1), their
@@ -879,42 +897,18 @@ hipError_t launch_reduce(const Plan& p, const Layout& L, char* ws, float* w_tile
 }
 
 hipError_t launch_write_outputs(const Plan& p, const Layout& L, char* ws, int32_t* w_keys, int32_t* pairs_out,
-                                int64_t n_pairs, int64_t n_w, hipStream_t s, bool dev_counts) {
-    const WsHeader* dn = dev_counts ? reinterpret_cast<const WsHeader*>(ws + L.hdr) : nullptr;
-    if (w_keys && p.nk[2] > 0 && n_w > 0) {
-        Unpack up{};
-        up.n = p.nk[2];
-        for (int c = 0; c < p.nk[2]; c++) up.bits[c] = p.w_bits[c];
-        k_write_keys<<<blocks_for(n_w), kThreads, 0, s>>>(reinterpret_cast<const uint64_t*>(ws + L.seg_key), n_w, up,
-                                                           w_keys, dn);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    if (pairs_out && n_pairs > 0) {
-        k_write_pairs<<<blocks_for(n_pairs), kThreads, 0, s>>>(reinterpret_cast<const int32_t*>(ws + L.pu),
-                                                                reinterpret_cast<const int32_t*>(ws + L.pv), n_pairs,
-                                                                pairs_out, dn);
-        return hipGetLastError();
-    }
-    return hipSuccess;
-}
-
-// The counts of an asynchronous call, from the join's header: counts[0] the
-// pairs, [1] the output keys, [2] a tre_status (key errors as on the host,
-// pairs beyond the workspace's capacity), [3] zero.
-__global__ void k_counts_out(const WsHeader* __restrict__ hdr, int64_t max_pairs, int64_t* __restrict__ counts) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    auto key_status = [](int32_t f) {
-        return (f & 4) ? int64_t(TRE_E_KEYRANGE) : (f & 1) ? int64_t(TRE_E_UNSORTED) : (f & 2) ? int64_t(TRE_E_DUPKEY) : 0;
-    };
-    int64_t st = key_status(hdr->err_u);
-    if (st == 0) st = key_status(hdr->err_v);
-    const int64_t n_pairs = hdr->n_pairs;
-    if (st == 0 && n_pairs > max_pairs) st = TRE_E_WORKSPACE;
-    counts[0] = n_pairs;
-    counts[1] = n_pairs > 0 ? hdr->n_w : 0;
-    counts[2] = st;
-    counts[3] = 0;
+                                int64_t n_pairs, int64_t n_w, hipStream_t s, bool dev_counts, int64_t* counts) {
+    if (p.nk[2] == 0) w_keys = nullptr;
+    const int64_t n = std::max<int64_t>({w_keys ? n_w : 0, pairs_out ? n_pairs : 0, counts ? 1 : 0});
+    if (n <= 0) return hipSuccess;
+    Unpack up{};
+    up.n = p.nk[2];
+    for (int c = 0; c < p.nk[2]; c++) up.bits[c] = p.w_bits[c];
+    k_outputs<<<blocks_for(n), kThreads, 0, s>>>(
+        reinterpret_cast<const uint64_t*>(ws + L.seg_key), n_w, up, w_keys, reinterpret_cast<const int32_t*>(ws + L.pu),
+        reinterpret_cast<const int32_t*>(ws + L.pv), n_pairs, pairs_out,
+        dev_counts ? reinterpret_cast<const WsHeader*>(ws + L.hdr) : nullptr, L.max_pairs, counts);
+    return hipGetLastError();
 }
 
 // The counts of a call that knew them on the host.
@@ -924,11 +918,6 @@ __global__ void k_counts_set(int64_t n_pairs, int64_t n_w, int64_t status, int64
     counts[1] = n_w;
     counts[2] = status;
     counts[3] = 0;
-}
-
-hipError_t launch_counts_out(const Layout& L, char* ws, int64_t max_pairs, int64_t* counts, hipStream_t s) {
-    k_counts_out<<<1, 64, 0, s>>>(reinterpret_cast<const WsHeader*>(ws + L.hdr), max_pairs, counts);
-    return hipGetLastError();
 }
 
 hipError_t launch_counts_set(int64_t n_pairs, int64_t n_w, int64_t status, int64_t* counts, hipStream_t s) {

@@ -72,6 +72,7 @@ struct TileArgs {
     int64_t w_elems;
     const int32_t *tWM, *tWN, *tWB;
     int32_t w_affine, w_sm;               // W(m, n) at m * w_sm + n
+    int32_t batched;                      // several batch indices (their offsets from the tB tables)
     int32_t K, mblocks, nblocks, blocks;  // blocks: of one unit (batch x m x n)
     int32_t waves;                        // wavefronts per block: 4 or 1
     const Unit* units;
@@ -344,8 +345,8 @@ __global__ __launch_bounds__(kThreads, 2) void k_gemm_tile(TileArgs g) {
     OpB ob;
     oa.init(g.a, m0, g.K, sAK);
     ob.init(g.b, n0, g.K, sBK);
-    const char* Ab = reinterpret_cast<const char*>(g.a.base) + int64_t(g.a.tB[batch]) * int(sizeof(T));
-    const char* Bb = reinterpret_cast<const char*>(g.b.base) + int64_t(g.b.tB[batch]) * int(sizeof(T));
+    const char* Ab = reinterpret_cast<const char*>(g.a.base) + int64_t(g.batched ? g.a.tB[batch] : 0) * int(sizeof(T));
+    const char* Bb = reinterpret_cast<const char*>(g.b.base) + int64_t(g.batched ? g.b.tB[batch] : 0) * int(sizeof(T));
     const int64_t a_bytes = g.a.elems * int(sizeof(T)), b_bytes = g.b.elems * int(sizeof(T));
     const const_i32* pa = (const const_i32*)g.a.idx;
     const const_i32* pb = (const const_i32*)g.b.idx;
@@ -508,7 +509,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_gemm_tile(TileArgs g) {
     };
     auto n_of = [&](int t) { return n0 + 32 * t + col; };
     float* out = un.slot < 0 ? g.W + int64_t(un.seg) * g.w_elems : g.partials + int64_t(un.slot) * g.w_elems;
-    const int32_t ob_w = g.tWB[batch];
+    const int32_t ob_w = g.batched ? g.tWB[batch] : 0;
     // this wavefront's registers r0 .. r1 of every tile (all of them, or its
     // quarter after the sums over the wavefronts)
     int r0 = 0, r1 = 16;
@@ -694,6 +695,7 @@ hipError_t launch_gemm_tile(const Plan& p, const Layout& L, char* ws, const void
     g.tWB = tb + p.table_off[T_WB];
     g.w_affine = p.tile_w_affine;
     g.w_sm = int32_t(p.tile_w_sm);
+    g.batched = p.nB > 1;
     g.K = int32_t(p.nK);
     g.mblocks = int32_t((M + 32 * p.tile_m - 1) / (32 * p.tile_m));
     g.nblocks = int32_t((N + 32 * p.tile_n - 1) / (32 * p.tile_n));

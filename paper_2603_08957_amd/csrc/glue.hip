@@ -120,6 +120,22 @@ hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s) {
     return hipGetLastError();
 }
 
+__global__ void k_fill_zero2(uint32_t* __restrict__ p, int64_t n, uint32_t* __restrict__ q, int64_t nq) {
+    const int64_t stride = int64_t(gridDim.x) * kThreads;
+    for (int64_t i = int64_t(blockIdx.x) * kThreads + threadIdx.x; i < n + nq; i += stride) {
+        if (i < n) p[i] = 0;
+        else q[i - n] = 0;
+    }
+}
+
+hipError_t launch_fill_zero2(void* p, size_t bytes, void* q, size_t q_bytes, hipStream_t s) {
+    const int64_t n = int64_t(bytes / 4), nq = int64_t(q_bytes / 4);
+    if (n + nq == 0) return hipSuccess;
+    k_fill_zero2<<<grid_for(n + nq, 4), kThreads, 0, s>>>(reinterpret_cast<uint32_t*>(p), n,
+                                                          reinterpret_cast<uint32_t*>(q), nq);
+    return hipGetLastError();
+}
+
 hipError_t launch_tiles_from_entries(const int64_t* slot, const int64_t* off, const void* val, int64_t n,
                                      int elem_bytes, void* tiles, int64_t n_tiles, int64_t tile_elems,
                                      hipStream_t s) {

@@ -70,6 +70,20 @@ struct ValSet {
     Radix rad[kValJobs];
 };
 
+__device__ inline int row_flags(const int32_t* row, bool has_prev, int r, const Radix& rad) {
+    int flags = 0;
+    for (int a = 0; a < r; a++)
+        if (row[a] < 0 || row[a] >= rad.r[a]) flags |= 4;
+    if (has_prev) {
+        const int32_t* prev = row - r;
+        int c = 0;
+        for (int a = 0; a < r && c == 0; a++) c = (prev[a] < row[a]) ? -1 : (prev[a] > row[a] ? 1 : 0);
+        if (c == 0) flags |= 2;
+        if (c > 0) flags |= 1;
+    }
+    return flags;
+}
+
 __global__ void k_validate(ValSet vs) {
     const int64_t b = blockIdx.x;
     int j = 0;
@@ -78,20 +92,17 @@ __global__ void k_validate(ValSet vs) {
     int64_t n = vs.n[j];
     if (vs.dn[j]) n = min(n, *vs.dn[j]);
     if (i >= n) return;
-    const int r = vs.r[j];
-    int flags = 0;
-    const int32_t* row = vs.keys[j] + i * r;
-    for (int a = 0; a < r; a++)
-        if (row[a] < 0 || row[a] >= vs.rad[j].r[a]) flags |= 4;
-    if (i > 0) {
-        const int32_t* prev = row - r;
-        int c = 0;
-        for (int a = 0; a < r && c == 0; a++) c = (prev[a] < row[a]) ? -1 : (prev[a] > row[a] ? 1 : 0);
-        if (c == 0) flags |= 2;
-        if (c > 0) flags |= 1;
-    }
+    const int flags = row_flags(vs.keys[j] + i * vs.r[j], i > 0, vs.r[j], vs.rad[j]);
     if (flags) atomicOr(vs.err[j], flags);
 }
+
+// The checks of one relation inside a join kernel that reads its keys anyway
+// (err null: none).  As launches of their own they read the keys once more:
+// 33.5 M two-attribute tuples took 150 us.
+struct ValRows {
+    int32_t* err;
+    Radix rad;
+};
 
 __global__ void k_pack_join(const int32_t* __restrict__ keys, int64_t n, int r, KeyDesc d, uint64_t* __restrict__ out,
                             uint32_t* __restrict__ perm) {
@@ -410,24 +421,42 @@ struct Radices {
 // payloads instead of the pair arrays.  With `first` (the key-space segment
 // search, zeroed; only when no sort follows), it also marks every W key's
 // first pair, as k_first_of_key would: first[k] = 1 + o.
+// Blocks from `dense_blocks` on check the rows of the inner relation (`ci`);
+// the outer relation's are checked where they are joined.
 template <typename KT, bool VO>
 __global__ void k_dense(const int32_t* __restrict__ okeys, int64_t n_o, int ro, KeyDesc dout, Radices ir,
                         const int32_t* __restrict__ ukeys, int ru, const int32_t* __restrict__ vkeys, int rv, WDesc wd,
                         int32_t* __restrict__ pu, int32_t* __restrict__ pv, KT* __restrict__ wk,
                         uint64_t* __restrict__ uv, WsHeader* __restrict__ hdr, int32_t* __restrict__ first,
-                        int64_t nk) {
+                        int64_t nk, int64_t dense_blocks, int64_t n_i, ValRows co, ValRows ci) {
+    if (int64_t(blockIdx.x) >= dense_blocks) {
+        const int64_t i = (int64_t(blockIdx.x) - dense_blocks) * blockDim.x + threadIdx.x;
+        if (i >= n_i) return;
+        const int r = VO ? ru : rv;
+        const int flags = row_flags((VO ? ukeys : vkeys) + i * r, i > 0, r, ci.rad);
+        if (flags) atomicOr(ci.err, flags);
+        return;
+    }
     const int64_t o = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (o >= n_o) return;
     if (o == 0) hdr->n_pairs = n_o;
-    if (dout.n == 1 && wd.n == 1 && wd.src[0] == (VO ? 1 : 0)) {
-        // one join label and W keyed by one label of the outer relation
-        // (whose keys okeys are): the pair's join key, its W key and the
-        // previous pair's W key are loaded at once (the general path below
-        // waits for each in turn)
-        const int32_t* row = okeys + o * ro;
-        const int32_t jk = row[dout.pos[0]];
-        const KT k = KT(uint32_t(row[wd.pos[0]]));
-        const KT kp = o > 0 ? KT(uint32_t(row[wd.pos[0] - ro])) : k;
+    const int32_t* row = okeys + o * ro;
+    if (ro == 2 && dout.n == 1 && wd.n == 1 && wd.src[0] == (VO ? 1 : 0)) {
+        // two attributes, one of them the join label and W keyed by one: both
+        // rows that the pair needs are loaded at once (the general path below
+        // waits for each value in turn)
+        const int32_t x0 = row[0], x1 = row[1];
+        const int32_t p0 = o > 0 ? row[-2] : x0, p1 = o > 0 ? row[-1] : x1;
+        if (co.err) {
+            int flags = (x0 < 0 || x0 >= co.rad.r[0] || x1 < 0 || x1 >= co.rad.r[1]) ? 4 : 0;
+            if (o > 0) {
+                if (p0 == x0 && p1 == x1) flags |= 2;
+                else if (p0 > x0 || (p0 == x0 && p1 > x1)) flags |= 1;
+            }
+            if (flags) atomicOr(co.err, flags);
+        }
+        const int32_t jk = dout.pos[0] ? x1 : x0;
+        const KT k = KT(uint32_t(wd.pos[0] ? x1 : x0)), kp = KT(uint32_t(wd.pos[0] ? p1 : p0));
         const int64_t in = min(max(jk, 0), ir.r[0] - 1);
         const int64_t u = VO ? in : o, v = VO ? o : in;
         wk[o] = k;
@@ -440,10 +469,14 @@ __global__ void k_dense(const int32_t* __restrict__ okeys, int64_t n_o, int ro, 
         if (first && uint64_t(k) < uint64_t(nk) && (o == 0 || kp != k)) first[k] = int32_t(o + 1);
         return;
     }
+    if (co.err) {
+        const int flags = row_flags(row, o > 0, ro, co.rad);
+        if (flags) atomicOr(co.err, flags);
+    }
     auto pair_of = [&](int64_t x, int64_t& u, int64_t& v) {
-        const int32_t* row = okeys + x * ro;
+        const int32_t* xr = okeys + x * ro;
         int64_t in = 0;
-        for (int i = 0; i < dout.n; i++) in = in * ir.r[i] + min(max(row[dout.pos[i]], 0), ir.r[i] - 1);
+        for (int i = 0; i < dout.n; i++) in = in * ir.r[i] + min(max(xr[dout.pos[i]], 0), ir.r[i] - 1);
         u = VO ? in : x;
         v = VO ? x : in;
     };
@@ -510,7 +543,20 @@ __global__ __launch_bounds__(kSmallThreads) void k_join_small(
     const int32_t* __restrict__ okeys, int64_t n_o, int ro, KeyDesc dout, const int32_t* __restrict__ ikeys,
     int64_t n_i, int ri, const int32_t* __restrict__ ukeys, int ru, const int32_t* __restrict__ vkeys, int rv,
     WDesc wd, int sort, int64_t cap, int32_t* __restrict__ pu, int32_t* __restrict__ pv,
-    int32_t* __restrict__ seg_start, uint64_t* __restrict__ seg_key, WsHeader* __restrict__ hdr) {
+    int32_t* __restrict__ seg_start, uint64_t* __restrict__ seg_key, WsHeader* __restrict__ hdr, int64_t n_u,
+    int64_t n_v, ValRows cu, ValRows cv) {
+    // the header's error words (nothing else of it is read before it is
+    // written) and the key checks, on the way
+    __shared__ int32_t s_err[2];
+    if (threadIdx.x < 2) s_err[threadIdx.x] = 0;
+    __syncthreads();
+    if (cu.err) {
+        int fu = 0, fv = 0;
+        for (int64_t i = threadIdx.x; i < n_u; i += kSmallThreads) fu |= row_flags(ukeys + i * ru, i > 0, ru, cu.rad);
+        for (int64_t i = threadIdx.x; i < n_v; i += kSmallThreads) fv |= row_flags(vkeys + i * rv, i > 0, rv, cv.rad);
+        if (fu) atomicOr(&s_err[0], fu);
+        if (fv) atomicOr(&s_err[1], fv);
+    }
     __shared__ int32_t s_off[kSmallMax + 1];
     __shared__ int32_t s_lo[kSmallMax];
     __shared__ uint64_t s_key[kSmallMax];  // W key << kSmallIdxBits | expansion index
@@ -649,6 +695,8 @@ __global__ __launch_bounds__(kSmallThreads) void k_join_small(
     if (t == 0) {
         seg_start[n_seg] = n;
         hdr->n_w = n_seg;
+        hdr->err_u = s_err[0];
+        hdr->err_v = s_err[1];
     }
 }
 
@@ -657,22 +705,55 @@ __global__ __launch_bounds__(kSmallThreads) void k_join_small(
 // its own group, in U order, so the pair list and the segments are written
 // directly and the counts are known on the host.
 // (n_dev: U's tuple count on the device, at most n_u; null: n_u)
-__global__ void k_keyed_by_u(const int32_t* __restrict__ ukeys, int64_t n_u, int ru, WDesc wd,
-                             int32_t* __restrict__ pu, int32_t* __restrict__ pv, int32_t* __restrict__ seg_start,
-                             uint64_t* __restrict__ seg_key, WsHeader* __restrict__ hdr,
-                             const int64_t* __restrict__ n_dev) {
+// The work units (one per key), the key checks and, in a single workgroup, the
+// header are written on the way: with a contraction whose offsets are affine
+// the whole EinSum is then three launches (4096-vertex chain, 64 keys: seven
+// before).
+constexpr int kKeyedOneMax = 1024;
+__global__ __launch_bounds__(kKeyedOneMax) void k_keyed_by_u(const int32_t* __restrict__ ukeys, int64_t n_u, int ru,
+                                                              WDesc wd, int32_t* __restrict__ pu,
+                                                              int32_t* __restrict__ pv, int32_t* __restrict__ seg_start,
+                                                              uint64_t* __restrict__ seg_key, Unit* __restrict__ units,
+                                                              WsHeader* __restrict__ hdr,
+                                                              const int64_t* __restrict__ n_dev, ValRows cu) {
     const int64_t u = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (n_dev) n_u = max<int64_t>(0, min(n_u, *n_dev));
-    if (u > n_u) return;
-    seg_start[u] = int32_t(u);
+    int flags = 0;
     if (u == n_u) {
+        seg_start[u] = int32_t(u);
         hdr->n_pairs = n_u;
         hdr->n_w = n_u;
+        hdr->n_units = n_u;
+        hdr->n_split = 0;
+        hdr->n_parts = 0;
+    } else if (u < n_u) {
+        const int32_t* row = ukeys + u * ru;
+        if (cu.err) flags = row_flags(row, u > 0, ru, cu.rad);
+        seg_start[u] = int32_t(u);
+        pu[u] = int32_t(u);
+        pv[u] = 0;
+        seg_key[u] = pack_w(row, row, wd);
+        Unit un;
+        un.seg = int32_t(u);
+        un.p0 = int32_t(u);
+        un.p1 = int32_t(u) + 1;
+        un.slot = -1;
+        units[u] = un;
+    }
+    if (gridDim.x > 1) {
+        if (flags) atomicOr(cu.err, flags);
         return;
     }
-    pu[u] = int32_t(u);
-    pv[u] = 0;
-    seg_key[u] = pack_w(ukeys + u * ru, ukeys + u * ru, wd);
+    // one workgroup: it writes the error words itself
+    __shared__ int32_t err;
+    if (threadIdx.x == 0) err = 0;
+    __syncthreads();
+    if (flags) atomicOr(&err, flags);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        hdr->err_u = err;
+        hdr->err_v = 0;
+    }
 }
 
 // Segments over a small key space (2^bits <= pairs): first[k] = 1 + the
@@ -809,6 +890,14 @@ KeyDesc desc_u(const Plan& p) {
     return d;
 }
 
+ValRows checks(const Plan& p, int op, WsHeader* hdr, bool validate) {
+    ValRows c{};
+    if (!validate) return c;
+    c.err = op == 0 ? &hdr->err_u : &hdr->err_v;
+    for (int a = 0; a < p.nk[op]; a++) c.rad.r[a] = p.radix[op][a];
+    return c;
+}
+
 KeyDesc desc_v(const Plan& p) {
     KeyDesc d{};
     d.n = p.n_join;
@@ -915,7 +1004,7 @@ namespace {
 
 template <typename KT>
 hipError_t group_impl(const Plan& p, const Layout& L, char* ws, const int32_t* u_keys, const int32_t* v_keys,
-                      int64_t cap, hipStream_t s) {
+                      int64_t cap, hipStream_t s, bool validate) {
     // every grid below is sized for the capacity; the kernels read the
     // pair count itself from the header
     WsHeader* hdr = reinterpret_cast<WsHeader*>(ws + L.hdr);
@@ -945,7 +1034,7 @@ hipError_t group_impl(const Plan& p, const Layout& L, char* ws, const int32_t* u
     const int64_t key_space = int64_t(1) << p.w_total_bits;
     const bool by_key = p.w_total_bits > 0 && p.w_total_bits <= 30 && key_space <= cap;
     int32_t* first = flags;  // key-space segment search: key_space + 1 <= cap + 1 entries
-    bool first_done = false;
+    bool first_done = false, first_zero = false;
     if (cap > 0 && (v_dense(p, L.n_u) || u_dense(p, L.n_v))) {
         const bool vo = v_dense(p, L.n_u);
         const int in_op = vo ? 0 : 1;  // the complete relation, indexed by the join key
@@ -953,15 +1042,23 @@ hipError_t group_impl(const Plan& p, const Layout& L, char* ws, const int32_t* u
         ir.n = p.nk[in_op];
         for (int i = 0; i < p.nk[in_op]; i++) ir.r[i] = p.radix[in_op][i];
         const bool mark = by_key && !sort;
-        if (mark && (e = launch_fill_zero(first, sizeof(int32_t) * size_t(key_space), s)) != hipSuccess) return e;
+        // the header and the key marks (which the sort leaves alone) in one launch
+        if ((e = launch_fill_zero2(hdr, sizeof(WsHeader), first, by_key ? sizeof(int32_t) * size_t(key_space) : 0, s)) !=
+            hipSuccess)
+            return e;
+        first_zero = by_key;
+        const ValRows cu = checks(p, 0, hdr, validate), cv = checks(p, 1, hdr, validate);
+        const int64_t n_o = vo ? L.n_v : L.n_u, n_i = vo ? L.n_u : L.n_v;
+        const int64_t db = int64_t(blocks_for(n_o)), blocks = db + (validate ? int64_t(blocks_for(n_i)) : 0);
+        if (blocks > int64_t(0x7fffffff)) return hipErrorInvalidConfiguration;
         if (vo)
-            k_dense<KT, true><<<blocks_for(L.n_v), kThreads, 0, s>>>(v_keys, L.n_v, p.nk[1], desc_v(p), ir, u_keys,
-                                                                     p.nk[0], v_keys, p.nk[1], wd, pu, pv, wk, uv, hdr,
-                                                                     mark ? first : nullptr, key_space);
+            k_dense<KT, true><<<unsigned(blocks), kThreads, 0, s>>>(v_keys, n_o, p.nk[1], desc_v(p), ir, u_keys, p.nk[0],
+                                                                    v_keys, p.nk[1], wd, pu, pv, wk, uv, hdr,
+                                                                    mark ? first : nullptr, key_space, db, n_i, cv, cu);
         else
-            k_dense<KT, false><<<blocks_for(L.n_u), kThreads, 0, s>>>(u_keys, L.n_u, p.nk[0], desc_u(p), ir, u_keys,
-                                                                      p.nk[0], v_keys, p.nk[1], wd, pu, pv, wk, uv, hdr,
-                                                                      mark ? first : nullptr, key_space);
+            k_dense<KT, false><<<unsigned(blocks), kThreads, 0, s>>>(u_keys, n_o, p.nk[0], desc_u(p), ir, u_keys, p.nk[0],
+                                                                     v_keys, p.nk[1], wd, pu, pv, wk, uv, hdr,
+                                                                     mark ? first : nullptr, key_space, db, n_i, cu, cv);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         first_done = mark;
     } else if (cap > 0 && p.v_outer && p.nk[0] == p.n_join) {
@@ -995,7 +1092,8 @@ hipError_t group_impl(const Plan& p, const Layout& L, char* ws, const int32_t* u
         // small key space: find the segments by key instead of by pair
         int32_t* kflags = reinterpret_cast<int32_t*>(ws + L.part_off);  // free until the work units are made
         if (!first_done) {
-            if ((e = launch_fill_zero(first, sizeof(int32_t) * size_t(key_space), s)) != hipSuccess) return e;
+            if (!first_zero && (e = launch_fill_zero(first, sizeof(int32_t) * size_t(key_space), s)) != hipSuccess)
+                return e;
             k_first_of_key<KT><<<blocks_for(cap), kThreads, 0, s>>>(wk, hdr, cap, key_space, first);
             if ((e = hipGetLastError()) != hipSuccess) return e;
         }
@@ -1035,7 +1133,7 @@ bool small_join_ok(const Plan& p, int64_t n_u, int64_t n_v, int64_t cap) {
 }
 
 hipError_t launch_join_small(const Plan& p, const Layout& L, char* ws, const int32_t* u_keys, const int32_t* v_keys,
-                             int64_t cap, hipStream_t s) {
+                             int64_t cap, hipStream_t s, bool validate) {
     WDesc wd{};
     wd.n = p.nk[2];
     for (int c = 0; c < p.nk[2]; c++) {
@@ -1049,14 +1147,15 @@ hipError_t launch_join_small(const Plan& p, const Layout& L, char* ws, const int
     uint64_t* seg_key = reinterpret_cast<uint64_t*>(ws + L.seg_key);
     WsHeader* hdr = reinterpret_cast<WsHeader*>(ws + L.hdr);
     const int sort = p.group_needs_sort ? 1 : 0;
+    const ValRows cu = checks(p, 0, hdr, validate), cv = checks(p, 1, hdr, validate);
     if (p.v_outer)
         k_join_small<true><<<1, kSmallThreads, 0, s>>>(v_keys, L.n_v, p.nk[1], desc_v(p), u_keys, L.n_u, p.nk[0],
                                                         u_keys, p.nk[0], v_keys, p.nk[1], wd, sort, cap, pu, pv,
-                                                        seg_start, seg_key, hdr);
+                                                        seg_start, seg_key, hdr, L.n_u, L.n_v, cu, cv);
     else
         k_join_small<false><<<1, kSmallThreads, 0, s>>>(u_keys, L.n_u, p.nk[0], desc_u(p), v_keys, L.n_v, p.nk[1],
                                                          u_keys, p.nk[0], v_keys, p.nk[1], wd, sort, cap, pu, pv,
-                                                         seg_start, seg_key, hdr);
+                                                         seg_start, seg_key, hdr, L.n_u, L.n_v, cu, cv);
     return hipGetLastError();
 }
 
@@ -1088,7 +1187,7 @@ bool keyed_by_u(const Plan& p) {
 }
 
 hipError_t launch_keyed_by_u(const Plan& p, const Layout& L, char* ws, const int32_t* u_keys, hipStream_t s,
-                             const int64_t* n_dev) {
+                             const int64_t* n_dev, bool validate) {
     WDesc wd{};
     wd.n = p.nk[2];
     for (int c = 0; c < p.nk[2]; c++) {
@@ -1096,18 +1195,24 @@ hipError_t launch_keyed_by_u(const Plan& p, const Layout& L, char* ws, const int
         wd.pos[c] = c;
         wd.bits[c] = p.w_bits[c];
     }
-    k_keyed_by_u<<<blocks_for(L.n_u + 1), kThreads, 0, s>>>(
+    WsHeader* hdr = reinterpret_cast<WsHeader*>(ws + L.hdr);
+    const bool one = L.n_u < kKeyedOneMax;
+    if (!one) {
+        const hipError_t e = launch_fill_zero(hdr, sizeof(WsHeader), s);
+        if (e != hipSuccess) return e;
+    }
+    k_keyed_by_u<<<one ? 1 : blocks_for(L.n_u + 1), one ? kKeyedOneMax : kThreads, 0, s>>>(
         u_keys, L.n_u, p.nk[0], wd, reinterpret_cast<int32_t*>(ws + L.pu), reinterpret_cast<int32_t*>(ws + L.pv),
         reinterpret_cast<int32_t*>(ws + L.seg_start), reinterpret_cast<uint64_t*>(ws + L.seg_key),
-        reinterpret_cast<WsHeader*>(ws + L.hdr), n_dev);
+        reinterpret_cast<Unit*>(ws + L.unit_desc), hdr, n_dev, checks(p, 0, hdr, validate));
     return hipGetLastError();
 }
 
 hipError_t launch_group(const Plan& p, const Layout& L, char* ws, const int32_t* u_keys, const int32_t* v_keys,
-                        int64_t cap, hipStream_t s) {
+                        int64_t cap, hipStream_t s, bool validate) {
     if (cap < 0 || cap > L.max_pairs) return hipErrorInvalidValue;
-    return p.w_total_bits <= 32 ? group_impl<uint32_t>(p, L, ws, u_keys, v_keys, cap, s)
-                                : group_impl<uint64_t>(p, L, ws, u_keys, v_keys, cap, s);
+    return p.w_total_bits <= 32 ? group_impl<uint32_t>(p, L, ws, u_keys, v_keys, cap, s, validate)
+                                : group_impl<uint64_t>(p, L, ws, u_keys, v_keys, cap, s, validate);
 }
 
 }  // namespace tre

@@ -225,19 +225,22 @@ bool u_dense(const Plan& p, int64_t n_v);
 // tuples and the capacity (min(workspace pairs, pair bound)) is at most 4096
 // pairs
 bool small_join_ok(const Plan& p, int64_t n_u, int64_t n_v, int64_t cap);
+// (writes the header; validate: checks both relations' keys)
 hipError_t launch_join_small(const Plan& p, const Layout& L, char* ws, const int32_t* u_keys, const int32_t* v_keys,
-                             int64_t cap, hipStream_t s);
+                             int64_t cap, hipStream_t s, bool validate);
 // V without promoted labels (one tuple) and W keyed by U's key as it is:
-// every U tuple is one pair and one group, written without counting
+// every U tuple is one pair and one group, written without counting, with the
+// header, the work units (one per key) and, with validate, U's key checks
 bool keyed_by_u(const Plan& p);
 hipError_t launch_keyed_by_u(const Plan& p, const Layout& L, char* ws, const int32_t* u_keys, hipStream_t s,
-                             const int64_t* n_dev = nullptr);
+                             const int64_t* n_dev, bool validate);
 // GROUP BY stage: the pair count is read on the device from the workspace
 // header (written by launch_join), clamped to the capacity `cap` (at most
 // L.max_pairs) that every grid is sized for, so the host launches it
-// without waiting
+// without waiting.  A dense join (v_dense, u_dense) is done here whole: the
+// header, the pairs and, with validate, both relations' key checks.
 hipError_t launch_group(const Plan& p, const Layout& L, char* ws, const int32_t* u_keys, const int32_t* v_keys,
-                        int64_t cap, hipStream_t s);
+                        int64_t cap, hipStream_t s, bool validate = false);
 
 // contract.hip
 hipError_t launch_tables(const Plan& p, int32_t* tables, hipStream_t s);
@@ -270,8 +273,8 @@ hipError_t launch_gemm_paced(const Plan& p, const Layout& L, char* ws, const voi
 hipError_t launch_reduce(const Plan& p, const Layout& L, char* ws, float* w_tiles, int64_t split_bound,
                          hipStream_t s);
 hipError_t launch_write_outputs(const Plan& p, const Layout& L, char* ws, int32_t* w_keys, int32_t* pairs_out,
-                                int64_t n_pairs, int64_t n_w, hipStream_t s, bool dev_counts = false);
-hipError_t launch_counts_out(const Layout& L, char* ws, int64_t max_pairs, int64_t* counts, hipStream_t s);
+                                int64_t n_pairs, int64_t n_w, hipStream_t s, bool dev_counts = false,
+                                int64_t* counts = nullptr);
 hipError_t launch_counts_set(int64_t n_pairs, int64_t n_w, int64_t status, int64_t* counts, hipStream_t s);
 
 // glue.hip
@@ -281,6 +284,8 @@ hipError_t launch_tiles_from_entries(const int64_t* slot, const int64_t* off, co
                                      int elem_bytes, void* tiles, int64_t n_tiles, int64_t tile_elems,
                                      hipStream_t s);
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
+// two arrays in one launch (sizes in bytes, multiples of 4; the second may be empty)
+hipError_t launch_fill_zero2(void* p, size_t bytes, void* q, size_t q_bytes, hipStream_t s);
 hipError_t launch_stack(const int32_t* keys, int64_t n, const void* tiles, int64_t row_elems, int32_t group,
                         int32_t elem_bytes, int32_t* out_keys, void* out_tiles, int64_t n_out, char* ws,
                         hipStream_t s, int stage);
