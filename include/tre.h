@@ -359,7 +359,7 @@ tre_status tre_stack_rows(const int32_t *keys, int64_t n, const void *tiles, int
  *                       source tile covers are zero.
  *   ws, ws_bytes      : device workspace, 256-byte aligned, at least
  *                       tre_repartition_workspace_bytes(...) (0 on bad arguments).
- * Synchronizes the stream twice.  TRE_E_CAPACITY (n_out set) if out_cap is
+ * Synchronizes the stream (once or twice).  TRE_E_CAPACITY (n_out set) if out_cap is
  * short; TRE_E_UNSORTED / TRE_E_DUPKEY / TRE_E_KEYRANGE for bad source keys. */
 size_t tre_repartition_workspace_bytes(const char *labels, const char *upper_in, const char *upper_out,
                                        const int64_t extent[26], const int32_t tile_in[26],
