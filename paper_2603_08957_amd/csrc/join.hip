@@ -1118,12 +1118,15 @@ hipError_t group_impl(const Plan& p, const Layout& L, char* ws, const int32_t* u
 }  // namespace
 
 bool small_join_ok(const Plan& p, int64_t n_u, int64_t n_v, int64_t cap) {
-    // joins whose pairs need the GROUP BY sort stay on the multi-kernel path:
-    // sorting 4096 pairs on one CU (a bitonic sort, 78 barrier stages) took
-    // longer than the device-wide radix sort it replaces (96 us against about
-    // 90 us for the whole multi-kernel join of the 4096-vertex chain's E1)
-    if (p.opt.small_join < 0 || p.v_needs_sort || p.group_needs_sort || keyed_by_u(p) || v_dense(p, n_u) ||
-        p.w_total_bits > 32)
+    // Joins whose pairs need the GROUP BY sort, or that index one relation by
+    // the join key, take the multi-kernel path (6 to 9 launches) but for very
+    // small ones: sorting 4096 pairs on one CU (a bitonic sort, 78 barrier
+    // stages) took 96 us, longer than that whole path, up to 1024 pairs (one
+    // step per thread and stage) it is the faster one by its launches: a call with 4,
+    // 280 and 961 pairs takes 51, 63 and 70 us, 95 to 97 on the multi-kernel path.
+    const int64_t n_max = std::max<int64_t>({n_u, n_v, cap});
+    if (p.opt.small_join < 0 || p.v_needs_sort || keyed_by_u(p) || p.w_total_bits > 32 ||
+        (n_max > kSmallThreads && (p.group_needs_sort || v_dense(p, n_u))))
         return false;
     // the inner relation's join keys, packed into one word each, are staged in LDS
     int join_bits = 0;
