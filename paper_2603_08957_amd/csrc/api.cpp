@@ -93,7 +93,7 @@ int32_t choose_pacing(const Plan& p, int64_t n_u, int64_t n_pairs, int64_t n_w, 
 // 256 for the vector class (several small units share a workgroup).
 double unit_workgroups(const Plan& p) {
     if (p.kclass == KC_GEMM) return double(blocks_per_unit(p));
-    const int64_t threads = (p.tile_elems[2] + p.vec_ept - 1) / p.vec_ept;
+    const int64_t threads = p.vec_dot ? p.tile_elems[2] * 16 : (p.tile_elems[2] + p.vec_ept - 1) / p.vec_ept;
     if (threads > 128) return double((threads + 255) / 256);
     int64_t t = 1;
     while (t < threads) t <<= 1;
@@ -342,7 +342,9 @@ tre_status contract_enqueue(tre_plan_t plan, const tre_join_result* jr, int64_t 
     // (a keyless one-tuple V with W keyed by U: one pair per key, nothing
     // to cut and no partial tiles to sum)
     const bool one_pair_keys = jr->n_v <= 1 && keyed_by_u(p);
-    const int64_t p_unit = (R > 1 || pace || one_pair_keys) ? n_pairs : choose_unit(p, L, n_pairs, n_w);
+    int64_t p_unit = (R > 1 || pace || one_pair_keys) ? n_pairs : choose_unit(p, L, n_pairs, n_w);
+    // (no key holds more than n_pairs - n_w + 1 pairs: nothing to cut)
+    if (!dev && p_unit > n_pairs - n_w) p_unit = n_pairs;
     hipError_t e;
     // (launch_units writes the tile offset tables itself)
     if (R > 1) {

@@ -127,6 +127,7 @@ struct Plan {
     // whether V's element is the same for a whole group of them
     int vec_ept = 1;
     bool vec_vbcast = false;
+    bool vec_dot = false, vec_dot_wide = false;  // k_vec_dot; with 16-byte loads
     bool vec_swap = false;  // vector class: the kernel's vector operand is V and its broadcast one U
     bool fast = false;
     bool fast_a_rowfast = false, fast_b_rowfast = false;
