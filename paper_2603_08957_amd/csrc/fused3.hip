@@ -693,6 +693,95 @@ __global__ __launch_bounds__(kThreads) void k3_masked(const float* __restrict__ 
     }
 }
 
+// The masked form with Q's rows in more than one XCD's L2 (4 MB): r is cut into
+// panels of `width`, each panel of all of Q fits one L2, and XCD x (workgroups
+// are dealt to the XCDs in turn) works on panels x, x + 8, ...: every row of a
+// panel comes from memory once and then from that L2, where whole rows are
+// fetched again for nearly every edge.  G lanes hold a triple's panel (16
+// bytes each); the panels' sums meet in k3_masked_sum, in panel order.
+// 398,808 edges between 13,752 nodes, rows of 1024 fp32 (3.3 GB of rows): 221
+// -> 135 us and 7 for the sums (panels of 2 MB, with more of them: 200).
+template <int G>
+__device__ inline float group_sum(float v) {
+    auto dpp = [](float x, auto ctrl) {
+        constexpr int kCtrl = decltype(ctrl)::value;
+        return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), kCtrl, 0xf, 0xf, true));
+    };
+    v += dpp(v, std::integral_constant<int, 0xb1>{});   // quad_perm: lane ^ 1
+    v += dpp(v, std::integral_constant<int, 0x4e>{});   // quad_perm: lane ^ 2
+    v += dpp(v, std::integral_constant<int, 0x141>{});  // row_half_mirror: the other four of eight
+    if constexpr (G >= 16) v += dpp(v, std::integral_constant<int, 0x140>{});  // row_mirror: the other eight
+    if constexpr (G >= 32) v += __shfl_xor(v, 16, 64);
+    return v;
+}
+
+constexpr int kPanelTriples = 4;  // of a group at a time
+constexpr int kPanelRounds = 4;
+
+template <int G>
+__global__ __launch_bounds__(kThreads) void k3_masked_panel(const float* __restrict__ P, const float* __restrict__ Q,
+                                                            const int32_t* __restrict__ tp,
+                                                            const int32_t* __restrict__ tq, int64_t nt, int64_t stride,
+                                                            int64_t R, int32_t width, int32_t panels, int64_t chunks,
+                                                            float* __restrict__ part) {
+    const int64_t i = int64_t(blockIdx.x) / 8;
+    const int panel = int(i / chunks) * 8 + int(blockIdx.x % 8);
+    if (panel >= panels) return;
+    constexpr int kGroups = kThreads / G;
+    const int g = int(threadIdx.x) / G, l = int(threadIdx.x) % G;
+    const int64_t r = int64_t(panel) * width + 4 * l;
+    const bool in = 4 * l < width && r < R;
+    const int64_t at = in ? r : 0;
+    // the groups of a workgroup take neighbouring triples in each round, so
+    // they meet in the rows of P (a group with triples of its own that keeps
+    // its P row in registers instead: 152 us)
+    const int64_t first = ((i % chunks) * (kPanelRounds * kGroups) + g) * kPanelTriples;
+#pragma unroll 2
+    for (int k = 0; k < kPanelRounds; k++) {
+        const int64_t t0 = first + k * (kGroups * kPanelTriples);
+        if (t0 >= nt) break;
+        // (the index arrays are padded to multiples of 256 bytes; past the
+        // end: the last triple again)
+        const int4 p4 = *reinterpret_cast<const int4*>(tp + t0), q4 = *reinterpret_cast<const int4*>(tq + t0);
+        int32_t ip[kPanelTriples] = {p4.x, p4.y, p4.z, p4.w}, iq[kPanelTriples] = {q4.x, q4.y, q4.z, q4.w};
+#pragma unroll
+        for (int b = 1; b < kPanelTriples; b++)
+            if (t0 + b >= nt) {
+                ip[b] = ip[b - 1];
+                iq[b] = iq[b - 1];
+            }
+        float4 x[kPanelTriples], y[kPanelTriples];
+#pragma unroll
+        for (int b = 0; b < kPanelTriples; b++) {
+            x[b] = *reinterpret_cast<const float4*>(P + int64_t(ip[b]) * R + at);
+            y[b] = *reinterpret_cast<const float4*>(Q + int64_t(iq[b]) * R + at);
+        }
+        float v[kPanelTriples];
+#pragma unroll
+        for (int b = 0; b < kPanelTriples; b++) {
+            float a = x[b].x * y[b].x;
+            a = fmaf(x[b].y, y[b].y, a);
+            a = fmaf(x[b].z, y[b].z, a);
+            a = fmaf(x[b].w, y[b].w, a);
+            v[b] = group_sum<G>(in ? a : 0.f);
+        }
+        if (l == 0) *reinterpret_cast<float4*>(part + int64_t(panel) * stride + t0) = make_float4(v[0], v[1], v[2], v[3]);
+    }
+}
+
+__global__ __launch_bounds__(kThreads) void k3_masked_sum(const float* __restrict__ part, int64_t stride,
+                                                          int32_t panels, const float* __restrict__ U,
+                                                          const int32_t* __restrict__ tu, int64_t nt, int64_t te_u,
+                                                          float* __restrict__ W) {
+    const int64_t t = int64_t(blockIdx.x) * kThreads + threadIdx.x;
+    if (t >= nt) return;
+    float dot = 0.f;
+#pragma unroll 8
+    for (int p = 0; p < panels; p++) dot += part[int64_t(p) * stride + t];
+    const float* u = U + int64_t(tu[t]) * te_u;
+    for (int64_t e = 0; e < te_u; e++) W[t * te_u + e] = u[e] * dot;
+}
+
 __global__ void k3_write_keys(const uint64_t* __restrict__ seg_key, int64_t n_w, F3Desc d, int32_t* __restrict__ out) {
     const int64_t q = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (q >= n_w) return;
@@ -925,6 +1014,40 @@ F3Layout f3_layout(const F3Desc& d, int64_t n_u) {
     return L;
 }
 
+// The masked contraction of nt triples; `part` has room for `part_floats` sums.
+// Panels where Q's rows exceed an L2 and are met at least four times each on
+// average, whole rounds of 8 panels of at least 128 bytes (else XCDs idle),
+// and one thread can write a tile.
+hipError_t launch_masked(const F3Desc& d, const float* U, const float* P, const float* Q, const int32_t* tu,
+                         const int32_t* tp, const int32_t* tq, int64_t nt, int64_t n_q, float* part,
+                         int64_t part_floats, float* W, hipStream_t s) {
+    const bool v4 = d.R % 4 == 0 && ((reinterpret_cast<uintptr_t>(P) | reinterpret_cast<uintptr_t>(Q)) & 15) == 0;
+    constexpr int64_t kL2 = int64_t(4) << 20;
+    constexpr int64_t kPanelBytes = kL2 - kL2 / 16;
+    const int64_t q_bytes = n_q * d.R * 4;
+    if (v4 && q_bytes > kL2 && nt / 4 >= n_q && d.te_u <= 4) {
+        const int64_t rounds = (q_bytes + 8 * kPanelBytes - 1) / (8 * kPanelBytes);
+        const int64_t width = ((d.R + 8 * rounds - 1) / (8 * rounds) + 15) / 16 * 16;
+        const int64_t panels = (d.R + width - 1) / width, stride = (nt + 3) / 4 * 4;
+        const int g = width <= 32 ? 8 : width <= 64 ? 16 : 32;
+        const int64_t per = int64_t(kThreads) / g * kPanelTriples * kPanelRounds;
+        const int64_t chunks = (nt + per - 1) / per, grid = (panels + 7) / 8 * 8 * chunks;
+        if (width >= 32 && width <= 128 && panels > 8 * (rounds - 1) + 6 && panels * stride <= part_floats &&
+            grid <= int64_t(0x7fffffff)) {
+            hipError_t e = launch_k(g == 8 ? k3_masked_panel<8> : g == 16 ? k3_masked_panel<16> : k3_masked_panel<32>,
+                                    dim3(unsigned(grid)), dim3(kThreads), 0, s, P, Q, tp, tq, nt, stride, int64_t(d.R),
+                                    int32_t(width), int32_t(panels), chunks, part);
+            if (e != hipSuccess) return e;
+            k3_masked_sum<<<blocks_for(nt), kThreads, 0, s>>>(part, stride, int32_t(panels), U, tu, nt, d.te_u, W);
+            return hipGetLastError();
+        }
+    }
+    const int64_t waves = (nt + kMaskedBatch - 1) / kMaskedBatch;
+    const dim3 grid{unsigned((waves + kThreads / 64 - 1) / (kThreads / 64))};
+    return launch_k(v4 ? k3_masked<true> : k3_masked<false>, grid, dim3(kThreads), 0, s, U, P, Q, tu, tp, tq, nt, d.te_u,
+                    d.R, W);
+}
+
 }  // namespace
 
 }  // namespace tre
@@ -1053,12 +1176,10 @@ tre_status tre_execute3(const char* einsum, const char* upper, const int64_t* ex
         tm.mark(s);
         const float* P = static_cast<const float*>(d.v_on_p ? v_tiles : x_tiles);
         const float* Q = static_cast<const float*>(d.v_on_p ? x_tiles : v_tiles);
-        const bool v4 = d.R % 4 == 0 && ((reinterpret_cast<uintptr_t>(P) | reinterpret_cast<uintptr_t>(Q)) & 15) == 0;
-        const int64_t waves = (nt + kMaskedBatch - 1) / kMaskedBatch;
-        const dim3 grid{unsigned((waves + kThreads / 64 - 1) / (kThreads / 64))};
         t_kernel_events = kep;
-        e = launch_k(v4 ? k3_masked<true> : k3_masked<false>, grid, dim3(kThreads), 0, s,
-                     static_cast<const float*>(u_tiles), P, Q, tu, tp, tq, nt, d.te_u, d.R, w_tiles);
+        // (nothing from wkey on is used in this form)
+        e = launch_masked(d, static_cast<const float*>(u_tiles), P, Q, tu, tp, tq, nt, n_q,
+                          static_cast<float*>(at(L.wkey)), int64_t((L.total - L.wkey) / sizeof(float)), w_tiles, s);
         t_kernel_events = nullptr;
         if (e != hipSuccess) return dev_fail(e, "masked contract");
         tm.mark(s);
@@ -1130,12 +1251,9 @@ tre_status tre_execute3(const char* einsum, const char* upper, const int64_t* ex
         if (nw > 0) {
             const float* P = static_cast<const float*>(d.v_on_p ? v_tiles : x_tiles);
             const float* Q = static_cast<const float*>(d.v_on_p ? x_tiles : v_tiles);
-            const bool v4 = d.R % 4 == 0 && ((reinterpret_cast<uintptr_t>(P) | reinterpret_cast<uintptr_t>(Q)) & 15) == 0;
-            const int64_t waves = (nt + kMaskedBatch - 1) / kMaskedBatch;
-            const dim3 grid{unsigned((waves + kThreads / 64 - 1) / (kThreads / 64))};
             t_kernel_events = kep;
-            e = launch_k(v4 ? k3_masked<true> : k3_masked<false>, grid, dim3(kThreads), 0, s,
-                         static_cast<const float*>(u_tiles), P, Q, tu, tp, tq, nt, d.te_u, d.R, w_tiles);
+            e = launch_masked(d, static_cast<const float*>(u_tiles), P, Q, tu, tp, tq, nt, n_q,
+                              static_cast<float*>(at(L.part)), int64_t((L.total - L.part) / sizeof(float)), w_tiles, s);
             t_kernel_events = nullptr;
             if (e != hipSuccess) return dev_fail(e, "masked contract");
         }

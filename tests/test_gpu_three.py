@@ -379,3 +379,46 @@ def test_dense_key_errors_gpu(masked):
     with pytest.raises(tre.TreError) as err:
         op(bad, ut, vk, vt, xk, xt, out=small)
     assert err.value.status == "TRE_E_KEYRANGE"
+
+
+@pytest.mark.parametrize("n_q,r,degree", [
+    (9001, 256, 5),    # 8 panels of 32
+    (4500, 384, 4),    # 8 panels of 48
+    (2100, 1000, 6),   # 8 panels of 128, the last one partial
+    (4093, 1024, 4),   # 8 panels of 128, whole
+    (13001, 512, 4),   # 8 panels of 64
+    (9001, 1024, 5),   # 16 panels of 64: two rounds
+    (9001, 160, 5),    # 32 wide would leave XCDs idle: whole rows
+    (9001, 256, 3),    # too few triples a row: whole rows
+])
+@pytest.mark.parametrize("te", [1, 3])
+def test_masked_panels(n_q, r, degree, te):
+    """S[m,i,j] = sum_r A[m,i,j] P[i,r] Q[j,r] with Q beyond one L2, against
+    float64: every width of a panel, counts that are no multiple of a group's
+    triples, every key there and some missing."""
+    import torch
+
+    import paper_2603_08957_amd as tre
+
+    rng = np.random.default_rng(n_q + r)
+    n_p = 700
+    for missing in (0, 5):
+        code = np.unique(rng.integers(0, n_p * n_q, n_q * degree + 3))
+        uk = np.stack([code // n_q, code % n_q], 1).astype(np.int32)
+        u = rng.standard_normal((len(code), te)).astype(np.float32)
+        p, q = rng.standard_normal((n_p, r)).astype(np.float32), rng.standard_normal((n_q, r)).astype(np.float32)
+        qk = np.arange(n_q, dtype=np.int32)[missing:]
+        ext = {"i": n_p, "j": n_q, "m": te, "r": r}
+        dev = [torch.from_numpy(np.ascontiguousarray(x)).cuda() for x in
+               (uk, u, np.arange(n_p, dtype=np.int32).reshape(-1, 1), p, qk.reshape(-1, 1), q[missing:])]
+        wk, wt, n = tre.execute3("mij,ir,jr->mij", "ij", ext, {"i": 1, "j": 1}, *dev)
+        there = uk[:, 1] >= missing
+        assert n == int(there.sum()) and np.array_equal(wk.cpu().numpy(), uk[there])
+        i, j = uk[there, 0], uk[there, 1]
+        ref, mag = np.zeros(len(i)), np.zeros(len(i))
+        for a in range(0, len(i), 8192):
+            x, y = p[i[a:a + 8192]].astype(np.float64), q[j[a:a + 8192]].astype(np.float64)
+            ref[a:a + 8192], mag[a:a + 8192] = (x * y).sum(1), np.abs(x * y).sum(1)
+        ref, mag = u[there] * ref[:, None], np.abs(u[there]) * mag[:, None]
+        # sums of up to 1024 products in pairs and panels: a few 2^-24 of the magnitudes
+        assert np.max(np.abs(wt.cpu().numpy().reshape(ref.shape) - ref) / mag) <= 8 * 2.0 ** -24
