@@ -49,13 +49,62 @@ __device__ inline T block_exclusive(T v, T* total) {
     return before + inc - v;
 }
 
+// Items base .. base + 15 of one thread, zero past the end: 16-byte loads and
+// stores where all are there (64 consecutive bytes or more per lane: an access
+// per item would touch every line of the wavefront's stretch 16 times; 10,486
+// items in one workgroup 12.5 -> 5.3 us, 65,536 in three launches 4.9 -> 3.5
+// each).
+template <typename T>
+__device__ inline void load_items(const T* in, int64_t base, int64_t n, T (&v)[kIpt]) {
+    constexpr int kV = 16 / int(sizeof(T));
+    typedef T vec __attribute__((ext_vector_type(kV)));
+    if (base + kIpt <= n && (reinterpret_cast<uintptr_t>(in) & 15) == 0) {
+#pragma unroll
+        for (int i = 0; i < kIpt / kV; i++) {
+            const vec x = reinterpret_cast<const vec*>(in + base)[i];
+#pragma unroll
+            for (int j = 0; j < kV; j++) v[kV * i + j] = x[j];
+        }
+        return;
+    }
+#pragma unroll
+    for (int i = 0; i < kIpt; i++) v[i] = (base + i < n) ? in[base + i] : T(0);
+}
+
+// v's items become their exclusive prefixes from `run` on, and are stored.
+template <typename T>
+__device__ inline void store_prefixes(T* out, int64_t base, int64_t n, T (&v)[kIpt], T run) {
+    constexpr int kV = 16 / int(sizeof(T));
+    typedef T vec __attribute__((ext_vector_type(kV)));
+#pragma unroll
+    for (int i = 0; i < kIpt; i++) {
+        const T x = v[i];
+        v[i] = run;
+        run += x;
+    }
+    if (base + kIpt <= n && (reinterpret_cast<uintptr_t>(out) & 15) == 0) {
+#pragma unroll
+        for (int i = 0; i < kIpt / kV; i++) {
+            vec x;
+#pragma unroll
+            for (int j = 0; j < kV; j++) x[j] = v[kV * i + j];
+            reinterpret_cast<vec*>(out + base)[i] = x;
+        }
+        return;
+    }
+#pragma unroll
+    for (int i = 0; i < kIpt; i++)
+        if (base + i < n) out[base + i] = v[i];
+}
+
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_tile_sum(const T* __restrict__ in, int64_t n, T* __restrict__ sums) {
     const int64_t base = int64_t(blockIdx.x) * kTile + int64_t(threadIdx.x) * kIpt;
+    T v[kIpt];
+    load_items(in, base, n, v);
     T s = 0;
 #pragma unroll
-    for (int i = 0; i < kIpt; i++)
-        if (base + i < n) s += in[base + i];
+    for (int i = 0; i < kIpt; i++) s += v[i];
     T total;
     (void)block_exclusive(s, &total);
     if (threadIdx.x == 0) sums[blockIdx.x] = total;
@@ -65,19 +114,13 @@ template <typename T>
 __global__ __launch_bounds__(kThreads) void k_tile_scan(const T* in, T* out, int64_t n, const T* __restrict__ tile_off) {
     const int64_t base = int64_t(blockIdx.x) * kTile + int64_t(threadIdx.x) * kIpt;
     T v[kIpt];
+    load_items(in, base, n, v);
     T s = 0;
 #pragma unroll
-    for (int i = 0; i < kIpt; i++) {
-        v[i] = (base + i < n) ? in[base + i] : T(0);
-        s += v[i];
-    }
+    for (int i = 0; i < kIpt; i++) s += v[i];
     T total;
-    T run = block_exclusive(s, &total) + (tile_off ? tile_off[blockIdx.x] : T(0));
-#pragma unroll
-    for (int i = 0; i < kIpt; i++) {
-        if (base + i < n) out[base + i] = run;
-        run += v[i];
-    }
+    const T run = block_exclusive(s, &total) + (tile_off ? tile_off[blockIdx.x] : T(0));
+    store_prefixes(out, base, n, v, run);
 }
 
 // Inputs of a few tiles: one workgroup of 1024 threads walks them in
@@ -95,12 +138,10 @@ __global__ __launch_bounds__(kOneThreads) void k_scan_one(const T* in, T* out, i
     for (int64_t c0 = 0; c0 < n; c0 += kOneChunk) {
         const int64_t base = c0 + int64_t(threadIdx.x) * kIpt;
         T v[kIpt];
+        load_items(in, base, n, v);
         T sum = 0;
 #pragma unroll
-        for (int i = 0; i < kIpt; i++) {
-            v[i] = (base + i < n) ? in[base + i] : T(0);
-            sum += v[i];
-        }
+        for (int i = 0; i < kIpt; i++) sum += v[i];
         const T inc = wave_inclusive(sum);
         if (lane == 63) wsum[w] = inc;
         __syncthreads();
@@ -112,12 +153,7 @@ __global__ __launch_bounds__(kOneThreads) void k_scan_one(const T* in, T* out, i
             all += x;
         }
         __syncthreads();
-        T run = carry + before + inc - sum;
-#pragma unroll
-        for (int i = 0; i < kIpt; i++) {
-            if (base + i < n) out[base + i] = run;
-            run += v[i];
-        }
+        store_prefixes<T>(out, base, n, v, carry + before + inc - sum);
         carry += all;
     }
 }
