@@ -1174,6 +1174,10 @@ bool u_dense(const Plan& p, int64_t n_v) {
 
 bool v_dense(const Plan& p, int64_t n_u) {
     if (!(p.nk[0] == p.n_join && p.nk[0] > 0) || (!p.v_outer && p.v_needs_sort)) return false;
+    // (the join key, in V's order, is U's index only where U lists the joined
+    // labels in that order too; V's order is then (u, v) order)
+    for (int i = 0; i < p.n_join; i++)
+        if (p.join_pos_u[i] != i) return false;
     int64_t space = 1;
     for (int i = 0; i < p.nk[0]; i++) {
         space *= p.radix[0][i];
