@@ -331,15 +331,18 @@ __global__ __launch_bounds__(kThreads, KS <= 2 ? 2 : 1) void k3_gemm(F3Args g) {
         }
         ctu = g.tu[ct];
     };
-    // ---- Q and P rows of triple t, column block rb, into buffer x & 1
+    // ---- Q and P rows of triple t, column block rb, into buffer x & 1 (the
+    // column block's place in 64 bits: with r outermost a tile holds up to 64 R
+    // elements; a lane's within the block in 32)
     auto copy_qp = [&](int32_t t, int rb, int64_t x) {
-        const int64_t r = min(rb * kCols + lane, d.R - 1);
-        const float* Qt = g.Q + int64_t(g.tq[t]) * d.te_q;
-        const float* Pt = g.P + int64_t(g.tp[t]) * d.te_p;
+        const int64_t r0 = int64_t(rb) * kCols;
+        const uint32_t col = uint32_t(min(int64_t(lane), d.R - 1 - r0));
+        const float* Qt = g.Q + int64_t(g.tq[t]) * d.te_q + r0 * d.q_sr;
+        const float* Pt = g.P + int64_t(g.tp[t]) * d.te_p + r0 * d.p_sr;
+        const uint32_t cq = col * uint32_t(d.q_sr) * 4u, cp = col * uint32_t(d.p_sr) * 4u;
         const uint32_t to = qp_lds + uint32_t(x & 1) * qp_bytes;
-        for (int row = w; row < tq; row += 4) lds_copy4(to + row * 256, Qt + row * d.q_sq, uint32_t(r * d.q_sr) * 4u);
-        for (int row = w; row < tp; row += 4)
-            lds_copy4(to + (tq + row) * 256, Pt + row * d.p_sp, uint32_t(r * d.p_sr) * 4u);
+        for (int row = w; row < tq; row += 4) lds_copy4(to + row * 256, Qt + row * d.q_sq, cq);
+        for (int row = w; row < tp; row += 4) lds_copy4(to + (tq + row) * 256, Pt + row * d.p_sp, cp);
     };
     copy_qp(ct, cblk % d.rblocks, i0);
     int rstage = 0;  // the stage whose chunk is being used

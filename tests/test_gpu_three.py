@@ -422,3 +422,39 @@ def test_masked_panels(n_q, r, degree, te):
         ref, mag = u[there] * ref[:, None], np.abs(u[there]) * mag[:, None]
         # sums of up to 1024 products in pairs and panels: a few 2^-24 of the magnitudes
         assert np.max(np.abs(wt.cpu().numpy().reshape(ref.shape) - ref) / mag) <= 8 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("side", ["p", "q"])
+def test_small_operand_above_4_gib(side):
+    """A small operand stored with r outermost, tiles of 64 x (2^24 + 70) fp32
+    (4.3 GB): byte offsets inside it need more than 32 bits."""
+    import torch
+
+    import paper_2603_08957_amd as tre
+
+    R, g = (1 << 24) + 70, torch.Generator(device="cuda").manual_seed(4)
+    tp, tq = (64, 4) if side == "p" else (2, 64)
+    t = torch.randn((1, 2, tp, tq), generator=g, device="cuda")
+    wide = torch.randn((R, 64), generator=g, device="cuda")  # [r, p] or [r, q]
+    other = torch.randn((tq if side == "p" else tp, R), generator=g, device="cuda")
+    e = "ijk,rj,kr->ir" if side == "p" else "ijk,jr,rk->ir"
+    b, c = (wide, other) if side == "p" else (other, wide)
+    k1 = torch.zeros((1, 1), dtype=torch.int32, device="cuda")
+    _, w, nt = tre.execute3(e, "jk", {"i": 2, "j": tp, "k": tq, "r": R}, {"j": tp, "k": tq},
+                            torch.zeros((1, 2), dtype=torch.int32, device="cuda"), t.reshape(1, -1),
+                            k1, b.reshape(1, -1), k1.clone(), c.reshape(1, -1))
+    assert nt == 1
+    w = w.reshape(2, R)
+    # columns around the place where a 32-bit byte offset wraps, and spread over all of them
+    at = torch.cat([torch.arange(0, 80), torch.arange((1 << 24) - 80, R), torch.randint(R, (4000,))]).cuda()
+    p = b[at].T if side == "p" else b[:, at]
+    q = c[:, at] if side == "p" else c[at].T
+    ref = torch.zeros((2, len(at)), dtype=torch.float64, device="cuda")
+    mag = torch.zeros_like(ref)
+    for i in range(tp):
+        for j in range(tq):
+            x = t[0, :, i, j].double()[:, None] * (p[i].double() * q[j].double())[None]
+            ref += x
+            mag += x.abs()
+    # exact products summed in fp32
+    assert float(((w[:, at].double() - ref).abs() / mag).max()) <= 32 * 2.0 ** -24
