@@ -346,7 +346,7 @@ __global__ __launch_bounds__(kThreads, KS <= 2 ? 2 : 1) void k3_gemm(F3Args g) {
     };
     copy_qp(ct, cblk % d.rblocks, i0);
     int rstage = 0;  // the stage whose chunk is being used
-    float mx = 0.f;
+    uint32_t lost = 0;
     Split8 fa[2];
     const int rsw = swizzle(c);
     auto read_t = [&](int stage, int s, float (&v)[8]) {
@@ -368,7 +368,7 @@ __global__ __launch_bounds__(kThreads, KS <= 2 ? 2 : 1) void k3_gemm(F3Args g) {
         float v[8];
         read_t(0, 0, v);
 #pragma unroll
-        for (int i = 0; i < 4; i++) fa[0].set(i, v[2 * i], v[2 * i + 1], mx);
+        for (int i = 0; i < 4; i++) fa[0].set(i, v[2 * i], v[2 * i + 1], lost);
     } else {
         lds_copy_wait<0>();
     }
@@ -398,7 +398,7 @@ __global__ __launch_bounds__(kThreads, KS <= 2 ? 2 : 1) void k3_gemm(F3Args g) {
                     if (!FULL && s == KS - 1) v[e] = k < tq ? v[e] : 0.f;
                 }
 #pragma unroll
-                for (int i = 0; i < 4; i++) fq[s][j].set(i, v[2 * i], v[2 * i + 1], mx);
+                for (int i = 0; i < 4; i++) fq[s][j].set(i, v[2 * i], v[2 * i + 1], lost);
             }
         float pv[2][2] = {};  // [parity of the step][column tile]
 #pragma unroll
@@ -411,7 +411,6 @@ __global__ __launch_bounds__(kThreads, KS <= 2 ? 2 : 1) void k3_gemm(F3Args g) {
 #pragma unroll
             for (int j = 0; j < 2; j++)
                 pv[A][j] = *reinterpret_cast<const float*>(buf + (tq + w + 4 * i) * 256 + (32 * j + c) * 4);
-            asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(mx) : "v"(pv[A][0]), "v"(pv[A][1]));
 #pragma unroll
             for (int s = 0; s < KS; s++) {
                 float v[8];
@@ -447,7 +446,7 @@ __global__ __launch_bounds__(kThreads, KS <= 2 ? 2 : 1) void k3_gemm(F3Args g) {
                             for (int r = r0; r < r1; r++) acc[j][r] = fmaf(pv[1 - A][j], y[1 - A][j][r], acc[j][r]);
                         }
                     }
-                    if (m >= 4 && m % 2 == 0) nx.set((m - 4) / 2, v[m - 4], v[m - 3], mx);
+                    if (m >= 4 && m % 2 == 0) nx.set((m - 4) / 2, v[m - 4], v[m - 3], lost);
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 fa[(s + 1) & 1] = nx;
@@ -540,9 +539,7 @@ __global__ __launch_bounds__(kThreads, KS <= 2 ? 2 : 1) void k3_gemm(F3Args g) {
 #pragma unroll
             for (int r = 0; r < 4; r++)
                 if (dst.row0 + row_of(r) < d.M && dst.col0 + 32 * j + c < d.R) check.add(res[j][r]);
-        // (three factors: inputs up to 2^16 keep a lost part, times the other
-        // two, below 2^-94)
-        bool redo = __ballot(check.bad(mx, 0x1p16f)) != 0;
+        bool redo = __ballot(check.bad(lost)) != 0;
         __syncthreads();
         if (lane == 0) red[w] = redo ? 1.f : 0.f;
         __syncthreads();

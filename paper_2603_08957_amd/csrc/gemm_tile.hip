@@ -428,7 +428,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_gemm_tile(TileArgs g) {
         trim_chunk<T, TN>(rb, ob.half, skip, end);
         cu.next();
     };
-    float mx = 0.f;
+    uint32_t lost = 0;
     auto run = [&](auto with_trim) {
         constexpr bool kTrim = decltype(with_trim)::value;
         begin();
@@ -447,11 +447,11 @@ __global__ __launch_bounds__(kThreads, 2) void k_gemm_tile(TileArgs g) {
 #pragma unroll
             for (int t = 0; t < TM; t++)
 #pragma unroll
-                for (int i = 0; i < 4; i++) fa[0][t].set(i, ra.v[t][2 * i], ra.v[t][2 * i + 1], mx);
+                for (int i = 0; i < 4; i++) fa[0][t].set(i, ra.v[t][2 * i], ra.v[t][2 * i + 1], lost);
 #pragma unroll
             for (int t = 0; t < TN; t++)
 #pragma unroll
-                for (int i = 0; i < 4; i++) fb[0][t].set(i, rb.v[t][2 * i], rb.v[t][2 * i + 1], mx);
+                for (int i = 0; i < 4; i++) fb[0][t].set(i, rb.v[t][2 * i], rb.v[t][2 * i + 1], lost);
             lds_read_wait();
             copy(0);
             for (int i = 0; i + 1 < n; i += 2) {
@@ -460,7 +460,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_gemm_tile(TileArgs g) {
                     wait_one();
                     fetch(1 - c, ra, rb);
                     if constexpr (kTrim) trim(ra, rb);
-                    split_mma_next(acc, fa[c], fb[c], ra.v, rb.v, fa[1 - c], fb[1 - c], mx, [&] {
+                    split_mma_next(acc, fa[c], fb[c], ra.v, rb.v, fa[1 - c], fb[1 - c], lost, [&] {
                         if constexpr (kDma) {
                             lds_read_wait();
                             copy(1 - c);
@@ -551,7 +551,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_gemm_tile(TileArgs g) {
         each([&](int i, int j, int r, int reg) {
             if (m_of(i, reg) < g.a.rows && n_of(j) < g.b.rows) check.add(acc[i][j][r]);
         });
-        bool redo = __ballot(check.bad(mx)) != 0;
+        bool redo = __ballot(check.bad(lost)) != 0;
         if (whole) {
             __syncthreads();  // the sums are read
             if (lane == 0) sums[w] = redo ? 1.f : 0.f;

@@ -1,24 +1,26 @@
 // fp32 products on the bf16 matrix cores.
 //
 // An fp32 value is the exact sum of three bf16 values, each the rest rounded
-// to nearest even: x = h + m + l with |m| <= 2^-9 |x| and |l| <= 2^-18 |x|
+// to nearest even: x = h + m + l with |m| <= 2^-8 |x| and |l| <= 2^-17 |x|
 // (24 significand bits, 8 per part).  A product is then the sum of nine exact
 // bf16 products (16 bits each, exact in fp32); the three smallest (m l, l m,
-// l l: together below 2^-26 of the product, a quarter of an fp32 rounding)
+// l l: together at most 2^-24 of the product, one fp32 rounding, and 2^-27.5
+// root mean square over random significands, where a rounding has 2^-25.3)
 // are left out and six are added in fp32 by v_mfma_f32_32x32x16_bf16, the
 // smallest first.  Six bf16 MFMAs of 32 cycles replace eight fp32 MFMAs of 64
 // for the same 32x32x16 block, so the matrix cores need 192 instead of 512
 // cycles; the splitting costs 6 vector instructions per element.
 //
-// Where the sum of the parts is not the value -- infinities, NaN, values that
-// round to infinity, parts below bf16's smallest normal value 2^-126 -- the
-// block is computed again by the fp32 MFMAs.  The kernels find that from
-// results and from the largest input: an infinity or NaN in any input (or a
-// part that became one) makes its results infinite or NaN; and with every
-// |x| <= 2^30 a lost part (below 2^-126) changes a K-term sum by at most K
-// 2^-96, less than 2^-24 of any result of at least 2^-50 for K up to 2^22.
-// So a block is kept when no result is infinite or NaN, none lies strictly
-// between 0 and 2^-50 and no input exceeds 2^30.
+// Where the sum of the parts is not the value the block is computed again by
+// the fp32 MFMAs.  There are two such cases, each found where it arises:
+//   the rest after h and m does not fit bf16 (bits below 2^-133, which only
+//     values below 2^-110 can have): the rest's lower 16 bits are collected in
+//     `lost`, in the one instruction that this costs per two values;
+//   an infinity or NaN in an input, or a part or sum that became one: the
+//     results that it enters are infinite or NaN.
+// The conversions and the MFMAs keep subnormal parts, products and sums, so
+// nothing else is lost, whatever the magnitudes: operands scaled by 1e-10 or
+// 1e10 stay on the bf16 MFMAs.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -33,20 +35,19 @@ typedef float split_f32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t split_u32x4 __attribute__((ext_vector_type(4)));
 typedef float split_f32x16 __attribute__((ext_vector_type(16)));
 
-constexpr float kSplitMaxInput = 0x1p30f;
-
 // Eight values of one row as MFMA operands.
 struct Split8 {
     split_u32x4 h, m, l;
-    // values 2 i and 2 i + 1; `mx` collects the largest magnitude
-    __device__ void set(int i, float x0, float x1, float& mx) {
-        asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(mx) : "v"(x0), "v"(x1));
+    // values 2 i and 2 i + 1; `lost` collects what their parts do not hold
+    __device__ void set(int i, float x0, float x1, uint32_t& lost) {
         const uint32_t hb = pack(x0, x1);
         const float r0 = x0 - __uint_as_float(hb << 16), r1 = x1 - __uint_as_float(hb & 0xffff0000u);
         const uint32_t mb = pack(r0, r1);
         h[i] = hb;
         m[i] = mb;
-        l[i] = pack(r0 - __uint_as_float(mb << 16), r1 - __uint_as_float(mb & 0xffff0000u));
+        const float l0 = r0 - __uint_as_float(mb << 16), l1 = r1 - __uint_as_float(mb & 0xffff0000u);
+        lost |= __float_as_uint(l0) | __float_as_uint(l1);
+        l[i] = pack(l0, l1);
     }
     static __device__ uint32_t pack(float a, float b) {
         return __builtin_bit_cast(uint32_t, __builtin_convertvector(split_f32x2{a, b}, split_bf16x2));
@@ -82,7 +83,7 @@ __device__ inline void split_mma(split_f32x16 (&acc)[TM][TN], const Split8 (&a)[
 template <int TM, int TN, typename Mid>
 __device__ inline void split_mma_next(split_f32x16 (&acc)[TM][TN], const Split8 (&a)[TM], const Split8 (&b)[TN],
                                       const float (&va)[TM][8], const float (&vb)[TN][8], Split8 (&na)[TM],
-                                      Split8 (&nb)[TN], float& mx, Mid mid) {
+                                      Split8 (&nb)[TN], uint32_t& lost, Mid mid) {
     constexpr int kSteps = kSplitSteps<TM, TN>, kPairs = 4 * (TM + TN);
     constexpr int kLead = TM * TN;  // MFMAs that cover the latency of the raw values' reads
 #pragma unroll
@@ -98,26 +99,18 @@ __device__ inline void split_mma_next(split_f32x16 (&acc)[TM][TN], const Split8 
 #pragma unroll
         for (int p = p0; p < p1; p++) {
             const int f = p / 4, i = p % 4;
-            if (f < TM) na[f].set(i, va[f][2 * i], va[f][2 * i + 1], mx);
-            else nb[f - TM].set(i, vb[f - TM][2 * i], vb[f - TM][2 * i + 1], mx);
+            if (f < TM) na[f].set(i, va[f][2 * i], va[f][2 * i + 1], lost);
+            else nb[f - TM].set(i, vb[f - TM][2 * i], vb[f - TM][2 * i + 1], lost);
         }
         __builtin_amdgcn_sched_barrier(0);
     }
 }
 
-// Collects whether every result lies where the split sum is as good as the
-// fp32 one: 0, or finite and at least 2^-50.
+// Whether a block's split sums stand: no result infinite or NaN, nothing lost.
 struct SplitCheck {
-    uint32_t top = 0, low = 0xffffffffu;
-    __device__ void add(float v) {
-        const uint32_t t = __float_as_uint(v) << 1;  // the magnitude's bits, doubled
-        top = max(top, t);
-        low = min(low, t - 1);  // zero wraps to the largest
-    }
-    __device__ bool bad(float max_input, float limit = kSplitMaxInput) const {
-        constexpr uint32_t kInf2 = 0xff000000u, kMin2 = uint32_t(127 - 50) << 24;
-        return top >= kInf2 || low < kMin2 - 1 || !(max_input <= limit);
-    }
+    uint32_t top = 0;
+    __device__ void add(float v) { top = max(top, __float_as_uint(v) << 1); }  // the magnitude's bits, doubled
+    __device__ bool bad(uint32_t lost) const { return top >= 0xff000000u || (lost & 0xffffu) != 0; }
 };
 
 }  // namespace tre

@@ -1,7 +1,7 @@
 """fp32 contractions on the bf16 matrix cores (csrc/split_f32.h): ordinary
 values to fp32 accuracy, and values the three-part split does not hold --
-infinities, NaN, magnitudes that round to infinity in bf16 or whose low parts
-fall below its smallest normal value -- computed as fp32, against float64."""
+infinities, NaN, magnitudes that round to infinity in bf16 or whose rest falls
+below its smallest value -- computed as fp32, against float64."""
 import numpy as np
 import pytest
 
@@ -152,3 +152,69 @@ def test_three_operands_split(kind):
     assert np.array_equal(np.isnan(got), np.isnan(ref))
     assert np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
     assert np.max(np.abs(got[fin] - ref[fin]) / mag[fin]) <= 32 * 2.0 ** -24
+
+
+# (scale of the first operand, of the second): subnormal values whose products
+# are not, values below bf16's smallest (2^-133), parts below its smallest
+# normal value, products and sums that are subnormal, and large ones
+SCALES = {
+    "subnormal": (1e-39, 1e9),
+    "subnormal_times_large": (1e-39, 1e30),
+    "below_bf16": (1e-42, 3e4),
+    "low_parts": (3e-36, 1e3),
+    "small": (1e-12, 1e-12),
+    "tiny_products": (1e-19, 1e-19),
+    "subnormal_products": (1e-20, 3e-21),
+    "large": (1e18, 1e18),
+}
+
+
+@pytest.mark.parametrize("scale", list(SCALES))
+@pytest.mark.parametrize("name", list(SHAPES))
+def test_split_magnitudes(name, scale):
+    """Operands scaled over fp32's range, some zeros among them, against float64."""
+    shape = SHAPES[name]
+    einsum, _, ext, _ = shape
+    ops = einsum.split("->")[0].split(",")
+    rng = np.random.default_rng(11)
+    a, b = ((rng.standard_normal([ext[c] for c in o]) * s).astype(np.float32) for o, s in zip(ops, SCALES[scale]))
+    a[rng.random(a.shape) < 0.2] = 0
+    _, got = run(shape, a, b)
+    ref = np.einsum(einsum, a.astype(np.float64), b.astype(np.float64))
+    mag = np.einsum(einsum, np.abs(a).astype(np.float64), np.abs(b).astype(np.float64))
+    # as above, and where products or sums are subnormal their roundings, at
+    # most 2^-150 each: six products and six sums for every k
+    assert np.all(np.abs(got - ref) <= 16 * 2.0 ** -24 * mag + 12 * ext["k"] * 2.0 ** -150)
+    if scale in ("subnormal", "subnormal_times_large", "below_bf16"):
+        assert np.count_nonzero(got) > 0.99 * got.size
+
+
+@pytest.mark.parametrize("scale", list(SCALES))
+def test_three_operands_magnitudes(scale):
+    import torch
+
+    sa, sb = SCALES[scale]
+    rng = np.random.default_rng(12)
+    ext, til = {"i": 70, "j": 24, "k": 64, "r": 70}, {"i": 35, "j": 12, "k": 16}
+    ids = np.sort(rng.choice(16, size=13, replace=False))
+    tk = np.stack([ids // 8, ids // 4 % 2, ids % 4], 1).astype(np.int32)
+    t = (rng.standard_normal((13, 35, 12, 16)) * sa).astype(np.float32)
+    t[rng.random(t.shape) < 0.2] = 0
+    b = rng.standard_normal((2, 12, 70)).astype(np.float32)
+    c = (rng.standard_normal((4, 16, 70)) * sb).astype(np.float32)
+    k = [torch.arange(n, dtype=torch.int32, device="cuda").reshape(n, 1) for n in (2, 4)]
+    wk, wt, nt = tre.execute3("ijk,jr,kr->ir", "ijk", ext, til, torch.from_numpy(tk).cuda(),
+                              torch.from_numpy(t.reshape(13, -1)).cuda(), k[0], torch.from_numpy(b.reshape(2, -1)).cuda(),
+                              k[1], torch.from_numpy(c.reshape(4, -1)).cuda())
+    assert nt == 13
+    rows, at = np.unique(tk[:, 0], return_inverse=True)
+    ref, mag, pmag = (np.zeros((len(rows), 35, 70)) for _ in range(3))
+    for s in range(13):
+        args = [x.astype(np.float64) for x in (t[s], b[tk[s, 1]], c[tk[s, 2]])]
+        ref[at[s]] += np.einsum("ijk,jr,kr->ir", *args)
+        mag[at[s]] += np.einsum("ijk,jr,kr->ir", *(np.abs(x) for x in args))
+        pmag[at[s]] += np.abs(args[1]).sum(0)[None]
+    got = wt.cpu().numpy().reshape(ref.shape)
+    # (the sums over k may be subnormal before the factor of the j operand meets them)
+    assert np.all(np.abs(got - ref) <= 32 * 2.0 ** -24 * mag + 12 * 16 * 2.0 ** -150 * (pmag + 13 * 12))
+    assert np.count_nonzero(got) > 0.99 * got.size
