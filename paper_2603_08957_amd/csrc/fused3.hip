@@ -346,7 +346,11 @@ __global__ __launch_bounds__(kThreads, KS <= 2 ? 2 : 1) void k3_gemm(F3Args g) {
     };
     copy_qp(ct, cblk % d.rblocks, i0);
     int rstage = 0;  // the stage whose chunk is being used
+    // what the split does not hold: of the T values so far (a triple's first
+    // fragment is split at the end of the one before), and whether there is
+    // something of the piece's Q values
     uint32_t lost = 0;
+    bool lost_q = false;
     Split8 fa[2];
     const int rsw = swizzle(c);
     auto read_t = [&](int stage, int s, float (&v)[8]) {
@@ -386,6 +390,7 @@ __global__ __launch_bounds__(kThreads, KS <= 2 ? 2 : 1) void k3_gemm(F3Args g) {
             copy_qp(wrap ? 0 : t + 1, wrap ? (rb + 1 == d.rblocks ? 0 : rb + 1) : rb, x + 1);
         }
         Split8 fq[KS][2];
+        uint32_t ql = 0;
 #pragma unroll
         for (int s = 0; s < KS; s++)
 #pragma unroll
@@ -398,8 +403,9 @@ __global__ __launch_bounds__(kThreads, KS <= 2 ? 2 : 1) void k3_gemm(F3Args g) {
                     if (!FULL && s == KS - 1) v[e] = k < tq ? v[e] : 0.f;
                 }
 #pragma unroll
-                for (int i = 0; i < 4; i++) fq[s][j].set(i, v[2 * i], v[2 * i + 1], lost);
+                for (int i = 0; i < 4; i++) fq[s][j].set(i, v[2 * i], v[2 * i + 1], ql);
             }
+        lost_q = lost_q || split_lost(ql);
         float pv[2][2] = {};  // [parity of the step][column tile]
 #pragma unroll
         for (int a = 0; a < 2; a++)
@@ -510,6 +516,7 @@ __global__ __launch_bounds__(kThreads, KS <= 2 ? 2 : 1) void k3_gemm(F3Args g) {
                              : g.part + (2 * int64_t(blockIdx.x) + (before ? 0 : 1)) * int64_t(kRows) * kCols;
         clear(acc[0]);
         clear(acc[1]);
+        lost_q = false;
         for (int64_t x = i; x < pend; x++) triple(x, t + int32_t(x - i), rb);
         // sum over the wavefronts, in the buffer of the piece's last Q and P:
         // wavefront w keeps registers 4 w .. 4 w + 3 of both column tiles
@@ -539,12 +546,26 @@ __global__ __launch_bounds__(kThreads, KS <= 2 ? 2 : 1) void k3_gemm(F3Args g) {
 #pragma unroll
             for (int r = 0; r < 4; r++)
                 if (dst.row0 + row_of(r) < d.M && dst.col0 + 32 * j + c < d.R) check.add(res[j][r]);
-        bool redo = __ballot(check.bad(lost)) != 0;
         __syncthreads();
-        if (lane == 0) red[w] = redo ? 1.f : 0.f;
-        __syncthreads();
-        redo = red[0] + red[1] + red[2] + red[3] != 0.f;
-        if (redo) {
+        // the largest value that meets one with something lost: of Q, and of T
+        // where Q's lost something, times the largest of P
+        float beside = 0.f;
+        if (split_lost(lost) || lost_q) {
+            float mx = 0.f, mp = 0.f;
+            const int64_t r = min(dst.col0 + lane, d.R - 1);
+            for (int32_t y = t; y < t + int32_t(pend - i); y++) {
+                const float* Tt = g.U + int64_t(g.tu[y]) * d.te_u + min(dst.row0 + c, d.M - 1) * KK;
+                const float* Pt = g.P + int64_t(g.tp[y]) * d.te_p + r * d.p_sr;
+                const float* Qt = g.Q + int64_t(g.tq[y]) * d.te_q + r * d.q_sr;
+                for (int k = 0; k < tq; k++) mx = fmaxf(mx, fabsf(Qt[k * d.q_sq]));
+                for (int k = 0; k < tp; k++) mp = fmaxf(mp, fabsf(Pt[k * d.p_sp]));
+                if (!lost_q) continue;
+                for (int k = w; k < tp; k += 4)
+                    for (int j = half; j < tq; j += 2) mx = fmaxf(mx, fabsf(Tt[k * tq + j]));
+            }
+            beside = split_wave_max(mx) * split_wave_max(mp);
+        }
+        if (split_bad_of_4(check, beside, red)) {
             clear(acc[0]);
             clear(acc[1]);
             for (int64_t x = i; x < pend; x++) triple_fp32(t + int32_t(x - i), dst.row0, dst.col0);

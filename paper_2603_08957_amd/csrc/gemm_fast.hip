@@ -343,9 +343,9 @@ __device__ inline void run_unit(const FastArgs& g, const Unit& un, int m0, int n
     }
 
     // The unit's sum over its pairs into acc; with `split` an fp32 product is
-    // taken on the bf16 matrix cores (split_f32.h), `lost` collecting
-    // what the split does not hold.
-    uint32_t lost = 0;
+    // taken on the bf16 matrix cores (split_f32.h), `mx` the largest
+    // value beside one that the split does not hold.
+    float mx = 0.f;
     auto run = [&](auto split, auto& pacer) {
         constexpr bool kSplit = decltype(split)::value;
 #pragma unroll
@@ -413,7 +413,7 @@ __device__ inline void run_unit(const FastArgs& g, const Unit& un, int m0, int n
                     frag8_f32<AROW>(As, oa[t], p, va[t]);
                     frag8_f32<BROW>(Bs, ob[t], p, vb[t]);
                 }
-                split_mma_next(acc, fa[1 - p], fb[1 - p], va, vb, fa[p], fb[p], lost, [] {});
+                split_mma_next(acc, fa[1 - p], fb[1 - p], va, vb, fa[p], fb[p], mx, [] {});
             } else {
                 bf16x8 a[2][2], b[2][2];
 #pragma unroll
@@ -459,7 +459,7 @@ __device__ inline void run_unit(const FastArgs& g, const Unit& un, int m0, int n
         // the waves agree through the ring's LDS, which no copy or read uses
         // any more (no LDS of its own: two workgroups share a CU's)
         int32_t* flag = reinterpret_cast<int32_t*>(lds);
-        const bool bad = __ballot(check.bad(lost)) != 0;
+        const bool bad = split_bad(check, mx);
         __syncthreads();
         if (lane == 0) flag[w] = bad;
         __syncthreads();

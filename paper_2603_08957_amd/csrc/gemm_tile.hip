@@ -428,7 +428,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_gemm_tile(TileArgs g) {
         trim_chunk<T, TN>(rb, ob.half, skip, end);
         cu.next();
     };
-    uint32_t lost = 0;
+    float mx = 0.f;
     auto run = [&](auto with_trim) {
         constexpr bool kTrim = decltype(with_trim)::value;
         begin();
@@ -444,14 +444,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_gemm_tile(TileArgs g) {
             wait_one();
             fetch(0, ra, rb);
             if constexpr (kTrim) trim(ra, rb);
-#pragma unroll
-            for (int t = 0; t < TM; t++)
-#pragma unroll
-                for (int i = 0; i < 4; i++) fa[0][t].set(i, ra.v[t][2 * i], ra.v[t][2 * i + 1], lost);
-#pragma unroll
-            for (int t = 0; t < TN; t++)
-#pragma unroll
-                for (int i = 0; i < 4; i++) fb[0][t].set(i, rb.v[t][2 * i], rb.v[t][2 * i + 1], lost);
+            split_all(ra.v, rb.v, fa[0], fb[0], mx);
             lds_read_wait();
             copy(0);
             for (int i = 0; i + 1 < n; i += 2) {
@@ -460,7 +453,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_gemm_tile(TileArgs g) {
                     wait_one();
                     fetch(1 - c, ra, rb);
                     if constexpr (kTrim) trim(ra, rb);
-                    split_mma_next(acc, fa[c], fb[c], ra.v, rb.v, fa[1 - c], fb[1 - c], lost, [&] {
+                    split_mma_next(acc, fa[c], fb[c], ra.v, rb.v, fa[1 - c], fb[1 - c], mx, [&] {
                         if constexpr (kDma) {
                             lds_read_wait();
                             copy(1 - c);
@@ -551,13 +544,13 @@ __global__ __launch_bounds__(kThreads, 2) void k_gemm_tile(TileArgs g) {
         each([&](int i, int j, int r, int reg) {
             if (m_of(i, reg) < g.a.rows && n_of(j) < g.b.rows) check.add(acc[i][j][r]);
         });
-        bool redo = __ballot(check.bad(lost)) != 0;
+        bool redo;
         if (whole) {
             __syncthreads();  // the sums are read
-            if (lane == 0) sums[w] = redo ? 1.f : 0.f;
+            redo = split_bad_of_4(check, mx, sums);
             __syncthreads();
-            redo = sums[0] + sums[1] + sums[2] + sums[3] != 0.f;
-            __syncthreads();
+        } else {
+            redo = split_bad(check, mx);
         }
         if (redo) {
             clear();

@@ -218,3 +218,64 @@ def test_three_operands_magnitudes(scale):
     # (the sums over k may be subnormal before the factor of the j operand meets them)
     assert np.all(np.abs(got - ref) <= 32 * 2.0 ** -24 * mag + 12 * 16 * 2.0 ** -150 * (pmag + 13 * 12))
     assert np.count_nonzero(got) > 0.99 * got.size
+
+
+def with_tails(kind, rng, a, b):
+    """a's contracted index last, b's first: values below bf16's grid (2^-133)
+    among ordinary ones, whose loss shows in no sum ("tails") or in every sum,
+    beside one row of huge values ("huge"), in a few places of one chunk."""
+    if kind == "tails":
+        a[rng.random(a.shape) < 0.5] *= np.float32(1e-43)
+        b[rng.random(b.shape) < 0.1] *= np.float32(1e-40)
+    else:
+        k = a.shape[-1] - 3
+        a *= np.float32(1e-6)
+        a[..., k] = np.float32(3e-43)
+        b[k] = np.float32(1e38)
+
+
+@pytest.mark.parametrize("kind", ["tails", "huge"])
+@pytest.mark.parametrize("name", ["gemm128_krow", "gemm128_long", "tile_krun_rows", "tile_waves"])
+def test_split_tails(name, kind):
+    shape = {**SHAPES, "gemm128_long": ("ik,kn->in", "ik", {"i": 128, "k": 1024, "n": 128}, {"i": 128, "k": 128}),
+             "tile_waves": ("ik,kn->in", "i", {"i": 40 * 3000, "k": 48, "n": 40}, {"i": 40})}[name]
+    einsum, _, ext, _ = shape
+    rng = np.random.default_rng(21)
+    a = rng.standard_normal((ext["i"], ext["k"])).astype(np.float32)
+    b = rng.standard_normal((ext["k"], ext["n"])).astype(np.float32)
+    with_tails(kind, rng, a, b)
+    _, got = run(shape, a, b)
+    ref = a.astype(np.float64) @ b.astype(np.float64)
+    mag = np.abs(a).astype(np.float64) @ np.abs(b).astype(np.float64)
+    assert np.max(np.abs(got - ref) / mag) <= 16 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("kind", ["tails", "huge", "huge_q"])
+def test_three_operands_tails(kind):
+    import torch
+
+    rng = np.random.default_rng(22)
+    ext, til = {"i": 64, "j": 24, "k": 80, "r": 70}, {"i": 32, "j": 12, "k": 40}
+    tk = np.stack(np.unravel_index(np.arange(8), (2, 2, 2)), 1).astype(np.int32)
+    t = rng.standard_normal((8, 32, 12, 40)).astype(np.float32)
+    b = rng.standard_normal((2, 12, 70)).astype(np.float32)
+    c = rng.standard_normal((2, 40, 70)).astype(np.float32)
+    if kind == "huge_q":  # the value that is lost is Q's
+        t[..., 7] = np.float32(1e38)
+        t[..., :7] *= np.float32(1e-6)
+        t[..., 8:] *= np.float32(1e-6)
+        c[:, 7] = np.float32(3e-43)
+    else:
+        for x in c:
+            with_tails(kind, rng, t, x)
+    k1 = torch.arange(2, dtype=torch.int32, device="cuda").reshape(2, 1)
+    _, wt, nt = tre.execute3("ijk,jr,kr->ir", "ijk", ext, til, torch.from_numpy(tk).cuda(),
+                             torch.from_numpy(t.reshape(8, -1)).cuda(), k1, torch.from_numpy(b.reshape(2, -1)).cuda(),
+                             k1.clone(), torch.from_numpy(c.reshape(2, -1)).cuda())
+    assert nt == 8
+    ref, mag = np.zeros((2, 32, 70)), np.zeros((2, 32, 70))
+    for s in range(8):
+        args = [x.astype(np.float64) for x in (t[s], b[tk[s, 1]], c[tk[s, 2]])]
+        ref[tk[s, 0]] += np.einsum("ijk,jr,kr->ir", *args)
+        mag[tk[s, 0]] += np.einsum("ijk,jr,kr->ir", *(np.abs(x) for x in args))
+    assert np.max(np.abs(wt.cpu().numpy().reshape(ref.shape) - ref) / mag) <= 32 * 2.0 ** -24
