@@ -343,8 +343,9 @@ tre_status contract_enqueue(tre_plan_t plan, const tre_join_result* jr, int64_t 
     // to cut and no partial tiles to sum)
     const bool one_pair_keys = jr->n_v <= 1 && keyed_by_u(p);
     int64_t p_unit = (R > 1 || pace || one_pair_keys) ? n_pairs : choose_unit(p, L, n_pairs, n_w);
-    // (no key holds more than n_pairs - n_w + 1 pairs: nothing to cut)
-    if (!dev && p_unit > n_pairs - n_w) p_unit = n_pairs;
+    // (no key holds more than n_pairs - n_w + 1 pairs, or more than the labels
+    // that W does not keep have values: nothing to cut)
+    if ((!dev && p_unit > n_pairs - n_w) || p_unit >= p.key_pairs_max) p_unit = n_pairs;
     hipError_t e;
     // (launch_units writes the tile offset tables itself)
     if (R > 1) {
@@ -375,11 +376,16 @@ tre_status contract_enqueue(tre_plan_t plan, const tre_join_result* jr, int64_t 
     t_kernel_events = nullptr;
     if (e != hipSuccess) return dev_fail(e, "contract");
     tm.mark(s);
-    if (R > 1 || p_unit < n_pairs) {
-        const int64_t split_bound = R > 1 ? n_w : std::min<int64_t>(n_w, n_pairs / (p_unit + 1) + 1);
+    // units as long as the average key or longer: outliers are cut, and their
+    // partial tiles summed on the way of the outputs
+    const bool outliers =
+        p.kclass == KC_GEMM && !p.fast && R <= 1 && p_unit < n_pairs && p_unit * n_w >= n_pairs;
+    const int64_t split_bound = R > 1 ? n_w : std::min<int64_t>(n_w, n_pairs / (p_unit + 1) + 1);
+    if ((R > 1 || p_unit < n_pairs) && !outliers) {
         if ((e = launch_reduce(p, L, w, w_tiles, split_bound, s)) != hipSuccess) return dev_fail(e, "reduce");
     }
-    if ((e = launch_write_outputs(p, L, w, w_keys, pairs_out, n_pairs, n_w, s, dev, counts)) != hipSuccess)
+    if ((e = launch_write_outputs(p, L, w, w_keys, pairs_out, n_pairs, n_w, s, dev, counts,
+                                  outliers ? w_tiles : nullptr, split_bound)) != hipSuccess)
         return dev_fail(e, "outputs");
     tm.mark(s);
     if (timing) {

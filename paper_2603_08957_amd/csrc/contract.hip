@@ -652,19 +652,32 @@ hipError_t vec_dispatch(const Plan& p, const VecArgs& a, dim3 grid, hipStream_t 
 
 constexpr int kReduceBatch = 8;
 
-__global__ __launch_bounds__(kThreads) void k_reduce(const int32_t* __restrict__ split, const WsHeader* hdr,
-                                                     const int32_t* __restrict__ poff, const float* __restrict__ parts,
-                                                     float* __restrict__ W, int64_t w_elems, int32_t w_bf16) {
-    const int64_t x = blockIdx.x;
-    if (x >= hdr->n_split) return;
-    const int32_t s = split[x];
-    const int32_t first = poff[s], cnt = poff[s + 1] - poff[s];
+struct Reduction {
+    const int32_t* split;    // the split keys
+    const int32_t* poff;     // key s: slots poff[s] .. poff[s + 1] - 1
+    const float* parts;
+    float* W;
+    int64_t w_elems;
+    int32_t w_bf16;
+};
+
+// Work per workgroup of one key: 256 lanes of 16 bytes (of 4 where the tile is
+// not a multiple of four).
+__host__ __device__ inline int64_t reduce_blocks(int64_t w_elems) {
+    return ((w_elems % 4 == 0 ? w_elems / 4 : w_elems) + kThreads - 1) / kThreads;
+}
+
+// Blocks b0, b0 + step, ... of split key x.
+__device__ inline void reduce_key(const Reduction& g, int64_t x, int64_t b0, int64_t step) {
+    const int32_t s = g.split[x];
+    const int32_t first = g.poff[s], cnt = g.poff[s + 1] - first;
+    const int64_t w_elems = g.w_elems;
     if (w_elems % 4 == 0) {
         // 16-byte lanes; partials are read once, so they bypass L2 retention
         // (a bf16 W takes the four sums of a lane as one 8-byte store)
         const int64_t q = w_elems / 4;
-        for (int64_t e = int64_t(blockIdx.y) * kThreads + threadIdx.x; e < q; e += int64_t(gridDim.y) * kThreads) {
-            const f32x4* src = reinterpret_cast<const f32x4*>(parts) + int64_t(first) * q + e;
+        for (int64_t e = b0 * kThreads + threadIdx.x; e < q; e += step * kThreads) {
+            const f32x4* src = reinterpret_cast<const f32x4*>(g.parts) + int64_t(first) * q + e;
             f32x4 acc = {0.f, 0.f, 0.f, 0.f};
             int j = 0;
             // eight partials in flight, added in slot order
@@ -676,18 +689,18 @@ __global__ __launch_bounds__(kThreads) void k_reduce(const int32_t* __restrict__
                 for (int i = 0; i < kReduceBatch; i++) acc += v[i];
             }
             for (; j < cnt; j++) acc += __builtin_nontemporal_load(src + int64_t(j) * q);
-            if (w_bf16) {
+            if (g.w_bf16) {
                 const uint32_t lo = uint32_t(f32_to_bf16_rne(acc[0])) | (uint32_t(f32_to_bf16_rne(acc[1])) << 16);
                 const uint32_t hi = uint32_t(f32_to_bf16_rne(acc[2])) | (uint32_t(f32_to_bf16_rne(acc[3])) << 16);
-                reinterpret_cast<uint2*>(W)[int64_t(s) * q + e] = make_uint2(lo, hi);
+                reinterpret_cast<uint2*>(g.W)[int64_t(s) * q + e] = make_uint2(lo, hi);
             } else {
-                reinterpret_cast<f32x4*>(W)[int64_t(s) * q + e] = acc;
+                reinterpret_cast<f32x4*>(g.W)[int64_t(s) * q + e] = acc;
             }
         }
         return;
     }
-    for (int64_t e = int64_t(blockIdx.y) * kThreads + threadIdx.x; e < w_elems; e += int64_t(gridDim.y) * kThreads) {
-        const float* src = parts + int64_t(first) * w_elems + e;
+    for (int64_t e = b0 * kThreads + threadIdx.x; e < w_elems; e += step * kThreads) {
+        const float* src = g.parts + int64_t(first) * w_elems + e;
         float acc = 0.f;
         int j = 0;
         for (; j + kReduceBatch <= cnt; j += kReduceBatch) {
@@ -698,9 +711,24 @@ __global__ __launch_bounds__(kThreads) void k_reduce(const int32_t* __restrict__
             for (int i = 0; i < kReduceBatch; i++) acc += v[i];
         }
         for (; j < cnt; j++) acc += src[int64_t(j) * w_elems];
-        if (w_bf16) reinterpret_cast<uint16_t*>(W)[int64_t(s) * w_elems + e] = f32_to_bf16_rne(acc);
-        else W[int64_t(s) * w_elems + e] = acc;
+        if (g.w_bf16) reinterpret_cast<uint16_t*>(g.W)[int64_t(s) * w_elems + e] = f32_to_bf16_rne(acc);
+        else g.W[int64_t(s) * w_elems + e] = acc;
     }
+}
+
+__global__ __launch_bounds__(kThreads) void k_reduce(Reduction g, const WsHeader* __restrict__ hdr) {
+    if (int64_t(blockIdx.x) < hdr->n_split) reduce_key(g, blockIdx.x, blockIdx.y, gridDim.y);
+}
+
+Reduction reduction(const Plan& p, const Layout& L, char* ws, float* w_tiles) {
+    Reduction g{};
+    g.split = reinterpret_cast<const int32_t*>(ws + L.split_list);
+    g.poff = reinterpret_cast<const int32_t*>(ws + L.part_off);
+    g.parts = reinterpret_cast<const float*>(ws + L.partials);
+    g.W = w_tiles;
+    g.w_elems = p.tile_elems[2];
+    g.w_bf16 = p.opt.w_bf16;
+    return g;
 }
 
 // ----------------------------------------------------------- outputs
@@ -714,11 +742,20 @@ struct Unpack {
 // null) its counts: [0] the pairs, [1] the output keys, [2] a tre_status (key
 // errors as on the host, pairs beyond the workspace's capacity), [3] zero.
 // (dn: the counts from the join's header, the host's being bounds)
-__global__ void k_outputs(const uint64_t* __restrict__ seg_key, int64_t n_w, Unpack up, int32_t* __restrict__ w_keys,
+// The first red_blocks workgroups sum the partial tiles of split keys (`red`;
+// rh: the header with their number): where only outliers are split, mostly
+// there are none, and a launch of its own would cost 2 us for nothing.
+__global__ __launch_bounds__(kThreads) void k_outputs(const uint64_t* __restrict__ seg_key, int64_t n_w, Unpack up, int32_t* __restrict__ w_keys,
                           const int32_t* __restrict__ pu, const int32_t* __restrict__ pv, int64_t n_pairs,
                           int32_t* __restrict__ pairs, const WsHeader* __restrict__ dn, int64_t max_pairs,
-                          int64_t* __restrict__ counts) {
-    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+                          int64_t* __restrict__ counts, Reduction red, int32_t red_blocks,
+                          const WsHeader* __restrict__ rh) {
+    if (int32_t(blockIdx.x) < red_blocks) {
+        const int64_t per = reduce_blocks(red.w_elems), all = int64_t(rh->n_split) * per;
+        for (int64_t b = blockIdx.x; b < all; b += red_blocks) reduce_key(red, b / per, b % per, per);
+        return;
+    }
+    const int64_t i = int64_t(blockIdx.x - red_blocks) * blockDim.x + threadIdx.x;
     if (counts && i == 0) {
         auto key_status = [](int32_t f) {
             return (f & 4) ? int64_t(TRE_E_KEYRANGE) : (f & 1) ? int64_t(TRE_E_UNSORTED) : (f & 2) ? int64_t(TRE_E_DUPKEY) : 0;
@@ -832,7 +869,8 @@ hipError_t launch_units(const Plan& p, const Layout& L, char* ws, int64_t n_pair
         if (total > kUnitsTableMax && (e = launch_tables(p, tables, s)) != hipSuccess) return e;
         k_units_small<<<1, kUnitsThreads, 0, s>>>(seg_start, n_w, std::max<int64_t>(p_unit, 1),
                                                    !longest_first || p.kclass != KC_GEMM ? 0
-                                                   : !p.fast && p_unit < n_pairs         ? 2
+                                                   // (units shorter than the average key: keys cut alike)
+                                                   : !p.fast && p_unit * n_w < n_pairs   ? 2
                                                                                          : 1,
                                                    reinterpret_cast<Unit*>(ws + L.unit_desc),
                                                    reinterpret_cast<int32_t*>(ws + L.split_list), nparts, hdr, ts,
@@ -944,28 +982,28 @@ hipError_t launch_contract(const Plan& p, const Layout& L, char* ws, const void*
 hipError_t launch_reduce(const Plan& p, const Layout& L, char* ws, float* w_tiles, int64_t split_bound,
                          hipStream_t s) {
     if (split_bound <= 0) return hipSuccess;
-    const int64_t we = p.tile_elems[2];
-    const int64_t lanes = we % 4 == 0 ? we / 4 : we;
-    const unsigned gy = unsigned(std::min<int64_t>((lanes + kThreads - 1) / kThreads, 65535));
-    k_reduce<<<dim3(unsigned(split_bound), gy), kThreads, 0, s>>>(
-        reinterpret_cast<const int32_t*>(ws + L.split_list), reinterpret_cast<const WsHeader*>(ws + L.hdr),
-        reinterpret_cast<const int32_t*>(ws + L.part_off), reinterpret_cast<const float*>(ws + L.partials), w_tiles,
-        we, p.opt.w_bf16);
+    const unsigned gy = unsigned(std::min<int64_t>(reduce_blocks(p.tile_elems[2]), 65535));
+    k_reduce<<<dim3(unsigned(split_bound), gy), kThreads, 0, s>>>(reduction(p, L, ws, w_tiles),
+                                                                  reinterpret_cast<const WsHeader*>(ws + L.hdr));
     return hipGetLastError();
 }
 
 hipError_t launch_write_outputs(const Plan& p, const Layout& L, char* ws, int32_t* w_keys, int32_t* pairs_out,
-                                int64_t n_pairs, int64_t n_w, hipStream_t s, bool dev_counts, int64_t* counts) {
+                                int64_t n_pairs, int64_t n_w, hipStream_t s, bool dev_counts, int64_t* counts,
+                                float* reduce_into, int64_t split_bound) {
     if (p.nk[2] == 0) w_keys = nullptr;
     const int64_t n = std::max<int64_t>({w_keys ? n_w : 0, pairs_out ? n_pairs : 0, counts ? 1 : 0});
-    if (n <= 0) return hipSuccess;
+    const int32_t red_blocks =
+        reduce_into ? int32_t(std::min<int64_t>(split_bound * reduce_blocks(p.tile_elems[2]), 1024)) : 0;
+    if (n <= 0 && red_blocks == 0) return hipSuccess;
     Unpack up{};
     up.n = p.nk[2];
     for (int c = 0; c < p.nk[2]; c++) up.bits[c] = p.w_bits[c];
-    k_outputs<<<blocks_for(n), kThreads, 0, s>>>(
+    const WsHeader* hdr = reinterpret_cast<const WsHeader*>(ws + L.hdr);
+    k_outputs<<<blocks_for(n) + unsigned(red_blocks), kThreads, 0, s>>>(
         reinterpret_cast<const uint64_t*>(ws + L.seg_key), n_w, up, w_keys, reinterpret_cast<const int32_t*>(ws + L.pu),
-        reinterpret_cast<const int32_t*>(ws + L.pv), n_pairs, pairs_out,
-        dev_counts ? reinterpret_cast<const WsHeader*>(ws + L.hdr) : nullptr, L.max_pairs, counts);
+        reinterpret_cast<const int32_t*>(ws + L.pv), n_pairs, pairs_out, dev_counts ? hdr : nullptr, L.max_pairs, counts,
+        reduction(p, L, ws, reduce_into), red_blocks, hdr);
     return hipGetLastError();
 }
 

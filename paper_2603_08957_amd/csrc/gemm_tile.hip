@@ -628,19 +628,26 @@ hipError_t dispatch(const Plan& p, const TileArgs& g, dim3 grid, size_t lds, hip
 // (fp32, both wavefronts of a SIMD busy) or 0.4 (bf16) for 2 x 2 MFMA tiles, a
 // block's start and end about 6 (its dependent index and tile loads, the
 // stores).
-static double tile_time(const Plan& p, double units, double chunks, int waves) {
+constexpr double kBlockTime = 6.0;
+static double tile_blocks(const Plan& p) {
     const double M = double(p.swap ? p.nN : p.nM), N = double(p.swap ? p.nM : p.nN);
-    const double blocks = double(p.nB) * std::ceil(M / (32 * p.tile_m)) * std::ceil(N / (32 * p.tile_n));
-    const double step = (p.dtype == TRE_BF16 ? 0.4 : 1.2) * p.tile_m * p.tile_n / 4.0;
+    return double(p.nB) * std::ceil(M / (32 * p.tile_m)) * std::ceil(N / (32 * p.tile_n));
+}
+static double chunk_time(const Plan& p) { return (p.dtype == TRE_BF16 ? 0.4 : 1.2) * p.tile_m * p.tile_n / 4.0; }
+static double tile_time(const Plan& p, double units, double chunks, int waves) {
     const double slots = 512.0 * kWaves / waves;
-    return std::ceil(units * blocks / slots) * (std::ceil(chunks / waves) * step + 6.0);
+    return std::ceil(units * tile_blocks(p) / slots) * (std::ceil(chunks / waves) * chunk_time(p) + kBlockTime);
 }
 
 // Unit length: keys are cut into c units each where that fills the chip's
 // rounds better than it costs in partial tiles (written and read once, at
 // about 4 TB/s, and one more launch).  On 320 keys of 256 pairs with two
 // 64 x 64 blocks, one unit per key leaves 640 workgroups for 512 places, two
-// rounds for the work of 1.25.
+// rounds for the work of 1.25.  Where that does not pay, keys much longer than
+// the average are still cut, so that none takes longer alone than the launch
+// would with its work spread evenly, twice an average key or a block's start
+// and end: of 401 keys one with 5,000 pairs of 32 x 48 tiles and the others
+// with 2 took 1,905 us uncut.
 int64_t tile_unit_pairs(const Plan& p, int64_t n_pairs, int64_t n_w) {
     const int64_t kc = p.dtype == TRE_BF16 ? kChunkK<uint16_t> : kChunkK<float>;
     const double per = double((p.nK + kc - 1) / kc), len = double(n_pairs) / double(std::max<int64_t>(n_w, 1));
@@ -650,11 +657,17 @@ int64_t tile_unit_pairs(const Plan& p, int64_t n_pairs, int64_t n_w) {
     int64_t unit = whole;
     for (int c = 1; c <= 64 && c <= len; c++) {
         const double pairs = std::ceil(len / c);
-        double t = std::min(tile_time(p, double(n_w) * c, pairs * per, kWaves), tile_time(p, double(n_w) * c, pairs * per, 1));
+        const double t4 = tile_time(p, double(n_w) * c, pairs * per, kWaves), t1 = tile_time(p, double(n_w) * c, pairs * per, 1);
+        double t = std::min(t4, t1);
         if (c > 1) t += 6.0 + double(n_w) * c * double(p.tile_elems[2]) * 8.0 / 4e6;
-        if (c == 1 || t < 0.95 * best) {
-            best = t;
-            unit = c == 1 ? whole : int64_t(pairs);
+        if (c > 1 && t >= 0.95 * best) continue;
+        best = t;
+        unit = int64_t(pairs);
+        if (c == 1) {
+            const double waves = t1 < t4 ? 1 : kWaves;
+            const double even = double(n_pairs) * tile_blocks(p) * waves / (512.0 * kWaves);
+            const double block = 2 * kBlockTime * waves / (per * chunk_time(p));
+            unit = int64_t(std::min(double(whole), std::ceil(std::max({2 * pairs, even, block}))));
         }
     }
     return unit;

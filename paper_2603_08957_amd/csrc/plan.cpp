@@ -167,6 +167,14 @@ static tre_status classify(Plan& p) {
         p.w_total_bits += p.w_bits[c];
     }
     if (p.w_total_bits > 64) { set_error("W key wider than 64 bits"); return TRE_E_SHAPE; }
+    // (a pair is the values of all promoted labels, W's among them)
+    p.key_pairs_max = 1;
+    for (int o = 0; o < 2; o++)
+        for (int a = 0; a < p.nk[o]; a++) {
+            const int l = p.klab[o][a];
+            if (find(p.klab[2], p.nk[2], l) >= 0 || (o == 1 && find(p.klab[0], p.nk[0], l) >= 0)) continue;
+            p.key_pairs_max = std::min<int64_t>(p.key_pairs_max, int64_t(1) << 31) * p.radix[o][a];
+        }
     // pairs come out of the join in (u, v) order: already grouped when W's
     // promoted labels are a prefix of U's key
     p.group_needs_sort = !(p.nk[2] == 0 || prefix_of_u);

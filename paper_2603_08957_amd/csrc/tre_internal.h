@@ -105,6 +105,7 @@ struct Plan {
     int w_src[26] = {}, w_pos[26] = {}, w_bits[26] = {};
     int w_total_bits = 0;
     bool group_needs_sort = false;
+    int64_t key_pairs_max = 1;  // most pairs of one W key: the key space of the promoted labels that W does not keep
     // join driven by V: W's key is V's key prefix and V's remaining key
     // attributes are the join labels, which U's key starts with; each V tuple
     // then meets one run of U tuples and the pairs come out in (W key, u, v)
@@ -275,7 +276,7 @@ hipError_t launch_reduce(const Plan& p, const Layout& L, char* ws, float* w_tile
                          hipStream_t s);
 hipError_t launch_write_outputs(const Plan& p, const Layout& L, char* ws, int32_t* w_keys, int32_t* pairs_out,
                                 int64_t n_pairs, int64_t n_w, hipStream_t s, bool dev_counts = false,
-                                int64_t* counts = nullptr);
+                                int64_t* counts = nullptr, float* reduce_into = nullptr, int64_t split_bound = 0);
 hipError_t launch_counts_set(int64_t n_pairs, int64_t n_w, int64_t status, int64_t* counts, hipStream_t s);
 
 // glue.hip

@@ -88,3 +88,38 @@ def test_many_short_units(dtype):
 def test_keys_split_between_units(dtype):
     o = check("ik,kn->in", "ik", {"i": 40, "k": 90 * 20, "n": 35}, {"i": 20, "k": 20}, dtype, max_pairs_per_unit=7)
     assert o.timing["n_partials"] > 0
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n_k,big,n", [(401, 1500, 1), (1300, 1200, 3), (70, 900, 2)])
+def test_keys_of_very_different_lengths(n_k, big, n, dtype):
+    """One to three keys of `big` pairs among keys of two: the long ones are cut
+    (their units' partial tiles summed with the outputs), the others are not."""
+    import torch
+
+    rng = np.random.default_rng(n_k)
+    tj, tk, feat = 20, 24, 33
+    keys = {(k, j) for k in range(n_k) for j in (3, 9)} | {(5 + 7 * i, j) for i in range(n) for j in range(big)}
+    vk = np.array(sorted(keys), dtype=np.int32)
+    u = rng.standard_normal((big, feat * tj)).astype(np.float32)
+    v = rng.standard_normal((len(vk), tk * tj)).astype(np.float32)
+    dev = [torch.from_numpy(x).cuda() for x in (u, v)]
+    if dtype == "bf16":
+        dev = [x.to(torch.bfloat16) for x in dev]
+        u, v = (x.float().cpu().numpy() for x in dev)
+    plan = tre.Plan("ij,kj->ki", "jk", {"i": feat, "j": big * tj, "k": n_k * tk}, {"j": tj, "k": tk}, dtype)
+    assert plan.kernel_class == "gemm"
+    uk = torch.arange(big, dtype=torch.int32, device="cuda").reshape(big, 1)
+    o = tre.einsum(plan, uk, dev[0], torch.from_numpy(vk).cuda(), dev[1], timing=True)
+    assert 0 < o.timing["n_split_segments"] <= n and o.n_w == n_k
+    ref, mag = np.zeros((n_k, tk, feat)), np.zeros((n_k, tk, feat))
+    for k in {5 + 7 * i for i in range(n)} | {0, 1, n_k - 1}:
+        at = np.flatnonzero(vk[:, 0] == k)
+        a = v[at].reshape(-1, tk, tj).transpose(1, 0, 2).reshape(tk, -1).astype(np.float64)
+        b = u[vk[at, 1]].reshape(-1, feat, tj).transpose(0, 2, 1).reshape(-1, feat).astype(np.float64)
+        ref[k], mag[k] = a @ b, np.abs(a) @ np.abs(b)
+        got = o.w_tiles[k].cpu().numpy().reshape(tk, feat)
+        # (30,000 products at most in one sum, in practice well below its square root)
+        assert np.max(np.abs(got - ref[k]) / mag[k]) <= 16 * 2.0 ** -24
+    assert torch.equal(o.w_keys.cpu()[:, 0], torch.arange(n_k, dtype=torch.int32))
+    assert bool((o.w_tiles.abs().sum(1) > 0).all())
