@@ -797,7 +797,8 @@ namespace {
 bool table_used(const Plan& p, int t) {
     if (p.kclass == KC_VEC) return t >= T_EU;
     if (p.fast || t >= T_EU) return false;
-    if (t == T_AM || t == T_AK || t == T_BN || t == T_BK) return p.tile_op[0].mode == TM_GATHER;
+    if (t == T_AM || t == T_AK || t == T_BN || t == T_BK)
+        return p.tile_op[0].mode == TM_GATHER || p.tile_op[0].mode == TM_GATHER8;
     if (t == T_WM || t == T_WN) return !p.tile_w_affine;
     return p.nB > 1;
 }

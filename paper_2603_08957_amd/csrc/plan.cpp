@@ -418,6 +418,16 @@ static tre_status classify(Plan& p) {
             else if (sr == 1 && on(4)) o.mode = TM_ROWS;
             o.wide = on(16) && (o.mode == TM_ROWS || p.nK >= k_chunk);
         };
+        // whether k 8 g .. 8 g + 7 are consecutive in the tile, on whole dwords
+        auto runs_of_8 = [&](const std::vector<int32_t>& tR, const std::vector<int32_t>& tK, const std::vector<int32_t>& tB,
+                             int64_t elems) {
+            const int32_t unit = p.dtype == TRE_BF16 ? 2 : 1;
+            bool ok = p.nK % 8 == 0 && elems % unit == 0;
+            for (int32_t x : tR) ok = ok && x % unit == 0;
+            for (int32_t x : tB) ok = ok && x % unit == 0;
+            for (size_t k = 0; k < tK.size() && ok; k++) ok = k % 8 ? tK[k] == tK[k - 1] + 1 : tK[k] % unit == 0;
+            return ok;
+        };
         p.tile_w_affine = affine(tWM, sWM) && affine(tWN, sWN) && sWN == 1;
         p.tile_w_sm = sWM;
         operand(p.tile_op[0], tAM, tAK, tAB, p.tile_elems[A]);
@@ -428,7 +438,10 @@ static tre_status classify(Plan& p) {
         auto staged = [](const TileOperand& o) { return o.mode == TM_K_RUN || o.mode == TM_ROWS; };
         if (!(staged(x) && staged(y))) {
             auto run = [&](const TileOperand& o) { return o.mode == TM_K_ODD || (o.mode == TM_K_RUN && p.nK >= k_chunk); };
-            x.mode = y.mode = run(x) && run(y) ? TM_K_ODD : TM_GATHER;
+            // (through the tables, but eight k a load where they lie together)
+            const bool odd = run(x) && run(y);
+            x.mode = odd ? TM_K_ODD : runs_of_8(tAM, tAK, tAB, p.tile_elems[A]) ? TM_GATHER8 : TM_GATHER;
+            y.mode = odd ? TM_K_ODD : runs_of_8(tBN, tBK, tBB, p.tile_elems[B]) ? TM_GATHER8 : TM_GATHER;
         }
     }
     return TRE_OK;

@@ -74,7 +74,7 @@ enum TableId { T_AM, T_AK, T_BK, T_BN, T_WM, T_WN, T_AB, T_BB, T_WB, T_EU, T_EV,
 enum KernelClass { KC_GEMM = 0, KC_VEC = 1 };
 
 // How k_gemm_tile loads an operand (see gemm_tile.hip).
-enum TileMode { TM_GATHER = 0, TM_K_RUN = 1, TM_K_ODD = 2, TM_ROWS = 3 };
+enum TileMode { TM_GATHER = 0, TM_K_RUN = 1, TM_K_ODD = 2, TM_ROWS = 3, TM_GATHER8 = 4 };
 struct TileOperand {
     int32_t mode = TM_GATHER;
     bool wide = false;       // 16-byte copies

@@ -123,3 +123,21 @@ def test_keys_of_very_different_lengths(n_k, big, n, dtype):
         assert np.max(np.abs(got - ref[k]) / mag[k]) <= 16 * 2.0 ** -24
     assert torch.equal(o.w_keys.cpu()[:, 0], torch.arange(n_k, dtype=torch.int32))
     assert bool((o.w_tiles.abs().sum(1) > 0).all())
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("b,j", [(1, 24), (3, 8), (2, 16), (5, 24), (4, 32)])
+def test_contracted_runs(b, j, dtype):
+    """Contracted indices in runs of eight that are not affine (labels b and j
+    apart), on one side, on the other and on both; K below and above a chunk."""
+    n = {"s": 3, "i": 37, "b": b, "j": j, "n": 35}
+    check("sbij,sbjn->sin", "s", n, {"s": 1}, dtype, keep=1.0)
+    check("sbjn,sbij->sin", "s", n, {"s": 1}, dtype, keep=1.0)
+    check("sbij,sbnj->sin", "s", n, {"s": 1}, dtype, keep=1.0)
+
+
+@pytest.mark.parametrize("k", [8, 24, 40, 64])
+def test_contracted_runs_beside_odd_rows(k):
+    # bf16 with an odd number of columns: element loads on one side only
+    check("ik,kn->in", "ik", {"i": 4 * 40, "k": 6 * k, "n": 47}, {"i": 40, "k": k}, "bf16", seed=k)
+    check("kn,ik->in", "ik", {"i": 4 * 40, "k": 6 * k, "n": 47}, {"i": 40, "k": k}, "bf16", seed=k)
