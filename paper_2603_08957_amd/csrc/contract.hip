@@ -626,16 +626,24 @@ __global__ __launch_bounds__(kThreads) void k_vec_dot(VecArgs a) {
     else a.W[int64_t(un.seg) * a.w_elems + e] = sum;
 }
 
-// Lanes per element: four loads of each operand in flight per lane at most.
+// Lanes per element: 4 where that fills the chip (65,536 elements are 16
+// wavefronts a CU) up to 32 loads of each operand per lane, and where one load
+// holds all; else 16 up to 4 loads, or 16 where 16,384 elements fill the chip;
+// else 64.  262,144 products of 24 fp32 elements: 11.5, 24.8 and 84.5 us with 4,
+// 16 and 64 lanes (an element per thread 29.7), of 129: 43, 32 and 89 (149), of 32
+// bf16: 12, 34 and 132 (36); 8,192 sums over 16 pairs of 129: 50, 26 and 26.
 template <typename T, int EPT>
 hipError_t dot_dispatch(const VecArgs& a, int64_t unit_bound, hipStream_t s) {
-    const int g = a.K > 16 * 4 * EPT ? 64 : 16;
-    const int64_t groups = unit_bound * a.w_elems, per = kThreads / g;
-    const int64_t blocks = (groups + per - 1) / per;
+    const int64_t groups = unit_bound * a.w_elems;
+    const int g = a.K <= 4 * EPT || (groups >= 65536 && a.K <= 32 * 4 * EPT)          ? 4
+                  : a.K <= 4 * 16 * EPT || (groups >= 16384 && a.K < 16 * 16 * EPT) ? 16
+                                                                                     : 64;
+    const int64_t per = kThreads / g, blocks = (groups + per - 1) / per;
     if (blocks > int64_t(0x7fffffff)) return hipErrorInvalidConfiguration;
     const dim3 grid{unsigned(blocks)}, block{unsigned(kThreads)};
-    return g == 64 ? launch_k(k_vec_dot<T, EPT, 64>, grid, block, 0, s, a)
-                   : launch_k(k_vec_dot<T, EPT, 16>, grid, block, 0, s, a);
+    return g == 4    ? launch_k(k_vec_dot<T, EPT, 4>, grid, block, 0, s, a)
+           : g == 16 ? launch_k(k_vec_dot<T, EPT, 16>, grid, block, 0, s, a)
+                     : launch_k(k_vec_dot<T, EPT, 64>, grid, block, 0, s, a);
 }
 
 template <typename T, int EPT>

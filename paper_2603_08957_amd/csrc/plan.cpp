@@ -351,7 +351,9 @@ static tre_status classify(Plan& p) {
         }
         // A long contraction over elements that are consecutive in both tiles:
         // lanes side by side along it instead of an element per lane
-        // (k_vec_dot).  Below 16 the lanes of a sum stay idle.
+        // (k_vec_dot).  From 16 on its 4 lanes per sum take less time than an
+        // element per thread, whatever the tile (262,144 sums of 16 fp32 values
+        // 10 and 21 us, of 16 bf16 12 and 21).
         if (p.vec_ept == 1 && p.nK >= 16) {
             p.vec_dot = true;
             for (size_t k = 0; k < tKU.size(); k++)

@@ -48,3 +48,29 @@ def test_grouped_by_u_then_v(orc, e, upper, keep):
         assert not plan.group_needs_sort
     ext = {c: (40 if c in "bij" else 8 if c in upper else 3) for c in ext}  # more pairs than one workgroup joins
     run(orc, e, upper, ext, {c: 1 for c in upper}, "f32", seed=4, keep=keep)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n", [256, 129, 40])
+def test_dot_many_elements(n, dtype):
+    """Enough sums to fill the chip with 4 lanes each (65,536), with 16 each
+    (16,384) and fewer, at and around the lengths where more lanes are taken,
+    against float64."""
+    import torch
+
+    import paper_2603_08957_amd as tre
+
+    g = torch.Generator(device="cuda").manual_seed(n)
+    keys = torch.cartesian_prod(torch.arange(n), torch.arange(n)).to(torch.int32).cuda()
+    vk = torch.arange(n, dtype=torch.int32, device="cuda").reshape(n, 1)
+    for k in (16, 17, 20, 31, 32, 33, 63, 64, 65, 127, 128, 129, 136, 255, 256, 257, 264, 512, 516, 520, 1024, 1032):
+        u, v = (torch.randn((m, k), generator=g, device="cuda") for m in (n * n, n))
+        if dtype == "bf16":
+            u, v = u.to(torch.bfloat16), v.to(torch.bfloat16)
+        plan = tre.Plan("ijk,jk->ij", "ij", {"i": n, "j": n, "k": k}, {"i": 1, "j": 1}, dtype)
+        assert plan.kernel_class == "vec"
+        o = tre.einsum(plan, keys, u, vk, v)
+        x = u.reshape(n, n, k).double() * v.double()[None]
+        err = (o.w_tiles.reshape(n, n).double() - x.sum(2)).abs() / x.abs().sum(2)
+        # exact bf16 products, rounded fp32 ones; sums in fp32
+        assert float(err.max()) <= 8 * 2.0 ** -24, k
