@@ -441,38 +441,50 @@ __global__ void k_dense(const int32_t* __restrict__ okeys, int64_t n_o, int ro, 
     if (o >= n_o) return;
     if (o == 0) hdr->n_pairs = n_o;
     const int32_t* row = okeys + o * ro;
-    if (ro == 2 && dout.n == 1 && wd.n == 1 && wd.src[0] == (VO ? 1 : 0)) {
-        // two attributes, one of them the join label and W keyed by one: both
-        // rows that the pair needs are loaded at once (the general path below
-        // waits for each value in turn)
-        const int32_t x0 = row[0], x1 = row[1];
-        const int32_t p0 = o > 0 ? row[-2] : x0, p1 = o > 0 ? row[-1] : x1;
-        if (co.err) {
-            int flags = (x0 < 0 || x0 >= co.rad.r[0] || x1 < 0 || x1 >= co.rad.r[1]) ? 4 : 0;
-            if (o > 0) {
-                if (p0 == x0 && p1 == x1) flags |= 2;
-                else if (p0 > x0 || (p0 == x0 && p1 > x1)) flags |= 1;
+    auto check_row = [&]() {
+        const int flags = row_flags(row, o > 0, ro, co.rad);
+        if (flags) atomicOr(co.err, flags);
+    };
+    if (dout.n == 1 && wd.n == 1 && wd.src[0] == (VO ? 1 : 0)) {
+        // one join label and W keyed by one label of the outer relation (whose
+        // keys okeys are): all values that the pair needs are loaded at once
+        // (the general path below waits for each in turn); of two attributes,
+        // the two rows whole, which are the key checks' too
+        int32_t jk, k0, kp0;
+        if (ro == 2) {
+            const int32_t x0 = row[0], x1 = row[1];
+            const int32_t p0 = o > 0 ? row[-2] : x0, p1 = o > 0 ? row[-1] : x1;
+            if (co.err) {
+                int flags = (x0 < 0 || x0 >= co.rad.r[0] || x1 < 0 || x1 >= co.rad.r[1]) ? 4 : 0;
+                if (o > 0) {
+                    if (p0 == x0 && p1 == x1) flags |= 2;
+                    else if (p0 > x0 || (p0 == x0 && p1 > x1)) flags |= 1;
+                }
+                if (flags) atomicOr(co.err, flags);
             }
-            if (flags) atomicOr(co.err, flags);
+            jk = dout.pos[0] ? x1 : x0;
+            k0 = wd.pos[0] ? x1 : x0;
+            kp0 = wd.pos[0] ? p1 : p0;
+        } else {
+            jk = row[dout.pos[0]];
+            k0 = row[wd.pos[0]];
+            kp0 = o > 0 ? row[wd.pos[0] - ro] : k0;
+            if (co.err) check_row();
         }
-        const int32_t jk = dout.pos[0] ? x1 : x0;
-        const KT k = KT(uint32_t(wd.pos[0] ? x1 : x0)), kp = KT(uint32_t(wd.pos[0] ? p1 : p0));
+        const KT k = KT(uint32_t(k0)), kp = KT(uint32_t(kp0));
         const int64_t in = min(max(jk, 0), ir.r[0] - 1);
         const int64_t u = VO ? in : o, v = VO ? o : in;
         wk[o] = k;
         if (uv) {
             uv[o] = (uint64_t(uint32_t(u)) << 32) | uint64_t(uint32_t(v));
-            return;
+        } else {
+            pu[o] = int32_t(u);
+            pv[o] = int32_t(v);
         }
-        pu[o] = int32_t(u);
-        pv[o] = int32_t(v);
         if (first && uint64_t(k) < uint64_t(nk) && (o == 0 || kp != k)) first[k] = int32_t(o + 1);
         return;
     }
-    if (co.err) {
-        const int flags = row_flags(row, o > 0, ro, co.rad);
-        if (flags) atomicOr(co.err, flags);
-    }
+    if (co.err) check_row();
     auto pair_of = [&](int64_t x, int64_t& u, int64_t& v) {
         const int32_t* xr = okeys + x * ro;
         int64_t in = 0;

@@ -36,3 +36,44 @@ def test_joined_labels_in_another_order(orc, idx, keep_v, small):
     spec = workloads.spec(e, upper, ext, til, "f32")
     _, out = gpu_run(spec, U, V, small_join=small)
     check(out, orc.run(orc.Plan(e, upper, ext, til), U, V), "f32")
+
+
+@pytest.mark.parametrize("small", [0, -1])
+@pytest.mark.parametrize("e,upper", [
+    ("jx,jx->jx", "j"),      # one attribute on the driving side
+    ("jx,jabx->ax", "jab"),  # three, V drives
+    ("abjx,jx->ax", "jab"),  # three and four, U drives
+    ("abcjx,jx->ax", "jabc"),
+    ("bjx,bx->jx", "jb"),    # grouped by the attribute that is not first: sorted
+])
+def test_dense_join_by_arity(orc, e, upper, small):
+    """One join label, W keyed by one label of the driving relation."""
+    import torch
+
+    import paper_2603_08957_amd as tre
+    from _parity import to_dev
+
+    ext = {"j": 9, "a": 7, "b": 6, "c": 5, "x": 2} if len(upper) > 2 else {"j": 40, "b": 37, "x": 2}
+    if e == "jx,jx->jx":
+        ext["j"] = 2000
+    ext, til = {c: n for c, n in ext.items() if c in e}, {c: 1 for c in upper}
+    la, lb = e.split("->")[0].split(",")
+    whole = "u" if la == "jx" else "v"  # the relation that holds every key
+    rng = np.random.default_rng(len(e))
+    U = workloads.random_relation(rng, la, upper, ext, til, "f32", 1.0 if whole == "u" else 0.7)
+    V = workloads.random_relation(rng, lb, upper, ext, til, "f32", 1.0 if whole == "v" else 0.7)
+    spec = workloads.spec(e, upper, ext, til, "f32")
+    plan, out = gpu_run(spec, U, V, small_join=small)
+    check(out, orc.run(orc.Plan(e, upper, ext, til), U, V), "f32")
+    # the driving relation's keys are checked on the way
+    drives = V if whole == "u" else U
+    for status, edit in (("TRE_E_KEYRANGE", lambda k: k[len(k) // 2].__setitem__(0, 10 ** 6)),
+                         ("TRE_E_DUPKEY", lambda k: k.__setitem__(5, k[4])),
+                         ("TRE_E_UNSORTED", lambda k: k.__setitem__([5, 6], k[[6, 5]]))):
+        bad = dict(drives, keys=drives["keys"].copy())
+        edit(bad["keys"])
+        a, b = (to_dev(U), to_dev(bad)) if whole == "u" else (to_dev(bad), to_dev(V))
+        with pytest.raises(tre.TreError) as err:
+            tre.einsum(plan, *a, *b)
+        assert err.value.status == status
+    torch.cuda.synchronize()
