@@ -968,8 +968,6 @@ hipError_t launch_join(const Plan& p, const Layout& L, char* ws, const int32_t* 
     int32_t* hist = reinterpret_cast<int32_t*>(ws + L.hist);
     const int64_t n_u = L.n_u, n_v = L.n_v;
     hipError_t e = hipSuccess;
-    // one pair per tuple of the driving relation, written by the GROUP BY stage
-    if (v_dense(p, n_u) || u_dense(p, n_v)) return hipSuccess;
     if (p.v_outer && p.nk[0] == p.n_join) {
         // walk V: each V tuple meets at most one U tuple (U's key is the join labels)
         int32_t* pos = reinterpret_cast<int32_t*>(ws + L.ucnt);
