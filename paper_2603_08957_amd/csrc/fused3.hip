@@ -1038,7 +1038,12 @@ F3Layout f3_layout(const F3Desc& d, int64_t n_u) {
 // The masked contraction of nt triples; `part` has room for `part_floats` sums.
 // Panels where Q's rows exceed an L2 and are met at least four times each on
 // average, whole rounds of 8 panels of at least 128 bytes (else XCDs idle),
-// and one thread can write a tile.
+// and one thread can write a tile.  They have to save more than their second
+// launch: 25 MB of rows met, and Q half as large again as an L2, or rows of up to
+// 256 (where the sums over 64 lanes are most of the other kernel's time).  The
+// call with 1,200 rows of 1,024 met 5, 12 and 30 times each takes 60, 62 and 68 us
+// in rows and 63, 64 and 72 in panels, 2,500 of 512 met 8 times 61 and 63; 5,000
+// of 256 met 16 times 72 and 68, 8,000 of 256 met 30 times 103 and 84.
 hipError_t launch_masked(const F3Desc& d, const float* U, const float* P, const float* Q, const int32_t* tu,
                          const int32_t* tp, const int32_t* tq, int64_t nt, int64_t n_q, float* part,
                          int64_t part_floats, float* W, hipStream_t s) {
@@ -1046,7 +1051,8 @@ hipError_t launch_masked(const F3Desc& d, const float* U, const float* P, const 
     constexpr int64_t kL2 = int64_t(4) << 20;
     constexpr int64_t kPanelBytes = kL2 - kL2 / 16;
     const int64_t q_bytes = n_q * d.R * 4;
-    if (v4 && q_bytes > kL2 && nt / 4 >= n_q && d.te_u <= 4) {
+    if (v4 && q_bytes > kL2 && nt / 4 >= n_q && d.te_u <= 4 && nt * d.R >= (int64_t(6) << 20) &&
+        (d.R <= 256 || q_bytes >= kL2 + kL2 / 2)) {
         const int64_t rounds = (q_bytes + 8 * kPanelBytes - 1) / (8 * kPanelBytes);
         const int64_t width = ((d.R + 8 * rounds - 1) / (8 * rounds) + 15) / 16 * 16;
         const int64_t panels = (d.R + width - 1) / width, stride = (nt + 3) / 4 * 4;

@@ -390,6 +390,8 @@ def test_dense_key_errors_gpu(masked):
     (9001, 1024, 5),   # 16 panels of 64: two rounds
     (9001, 160, 5),    # 32 wide would leave XCDs idle: whole rows
     (9001, 256, 3),    # too few triples a row: whole rows
+    (1200, 1024, 12),  # little more than an L2, long rows: whole rows
+    (4500, 256, 9),    # the same with short ones: 8 panels of 32
 ])
 @pytest.mark.parametrize("te", [1, 3])
 def test_masked_panels(n_q, r, degree, te):
