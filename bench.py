@@ -20,13 +20,14 @@ of the timed region.  Prints one JSON line:
               HIP events on the launch stream inside the timed region
   cpu_baseline the CPU oracle timed on a bounded sample of the same inputs,
               with the host's CPU count and model
-  configs     the same report for every workload (1-6), the headline first:
-              step time (mean, median, min over the timed steps), the
-              dominant kernel's roofline, and per EinSum its join,
-              contraction and reduction times with their algorithmic HBM
-              rates as fractions of 8 TB/s, its whole-EinSum roofline
-              fraction, and the read-once and per-pair byte bounds
-With --config N only that workload runs (no configs list).
+  einsums     per EinSum its join, contraction and reduction times
+  configs     every workload (1-6), the headline first: step time (mean and
+              median over the timed steps), rate, the dominant kernel and its
+              roofline fraction
+With --config N only that workload runs (no configs list).  --report FILE also
+writes the full report: for every workload every step's time, and per EinSum
+the phases' algorithmic HBM rates as fractions of 8 TB/s, its whole-EinSum
+roofline fraction, and the read-once and per-pair byte bounds.
 """
 from __future__ import annotations
 
@@ -56,6 +57,34 @@ SETTLE_S, SETTLE_S_PER_GIB = 0.5, 0.03  # pause after a workload's inputs are bu
 
 def log(*a):
     print(*a, file=sys.stderr, flush=True)
+
+
+def _short(x):
+    """Floats to six digits, in dicts and lists too."""
+    if isinstance(x, float):
+        return float(f"{x:.6g}")
+    if isinstance(x, dict):
+        return {k: _short(v) for k, v in x.items()}
+    return [_short(v) for v in x] if isinstance(x, list) else x
+
+
+LINE_EINSUM_KEYS = ("name", "einsum", "kernel_class", "n_pairs", "n_w", "ms", "roofline_frac", "join_ms", "contract_ms",
+                    "contract_roofline_frac", "reduce_ms", "contract_path")
+
+
+def line_of(out):
+    """The printed line: the report without the single steps' times, of the
+    EinSums the phase times, of the other workloads one short entry each (at
+    most some 6 KB: whoever keeps only the end of a log keeps all of it)."""
+    line = {k: v for k, v in out.items() if k not in ("timed_region", "einsums", "configs")}
+    line["timed_region"] = {k: v for k, v in out["timed_region"].items() if not isinstance(v, list)}
+    line["einsums"] = [{k: e[k] for k in LINE_EINSUM_KEYS if k in e} for e in out["einsums"]]
+    if "configs" in out:
+        line["configs"] = [{"config": c["config"], "dtype": c["dtype"], "ms_per_step": c["ms_per_step"],
+                            "ms_per_step_median": c["ms_per_step_median"], "value": c["value"], "unit": c["unit"],
+                            "kernel": c["roofline"]["kernel"], "kernel_ms": c["roofline"]["kernel_ms"],
+                            "bound": c["roofline"]["bound"], "frac": c["roofline"]["frac"]} for c in out["configs"]]
+    return {k: _short(v) if k not in ("value", "ms_per_step") else v for k, v in line.items()}
 
 
 def dev_rel(rel, torch):
@@ -1235,6 +1264,8 @@ def main():
     ap.add_argument("--config", type=int, default=0,
                     help="one workload 1..6 only (default: the headline workload 2, the bf16 GNN chain on 262,144 "
                          "vertices, then every other workload in a 'configs' list of the same line)")
+    ap.add_argument("--report", metavar="FILE",
+                    help="also write the full report (every step's time, every EinSum's phases) as JSON to FILE")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--cpu-budget", type=float, default=0.0, metavar="S",
                     help="seconds of oracle time per workload (default 6 for the headline, 3 for the others)")
@@ -1320,7 +1351,10 @@ def main():
     }
     if len(reports) > 1:
         out["configs"] = [{k: v for k, v in r.items()} for r in reports]
-    print(json.dumps(out), flush=True)
+    if args.report:
+        with open(args.report, "w") as f:
+            json.dump(out, f, indent=1)
+    print(json.dumps(line_of(out)), flush=True)
 
 
 if __name__ == "__main__":

@@ -136,3 +136,25 @@ def test_relation_from_coo(bench):
     r = bench.relation_from_coo(coords, vals, "jk", set(), ext, 1 << 20, "f32")
     assert r["keys"].shape == (1, 0) and r["tiles"].reshape(4, 6)[3, 2] == 4.0
     assert bench.relation_from_coo(coords, vals, "jk", set(), ext, 64, "f32") is None
+
+
+def test_line_is_short_and_whole(bench):
+    """The printed line holds what it has to and stays below 7,000 characters,
+    for every workload and many steps."""
+    einsum = {k: 123.456789012345 for k in bench.LINE_EINSUM_KEYS} | {"join_alg_bytes": 10 ** 12, "extra": "x" * 500}
+    roofline = {"bound": "hbm", "achieved": 751.7887192854558, "peak": 8000.0, "unit": "GB/s", "frac": 0.0939735899106,
+                "traffic": {"bytes": 10 ** 11}, "kernel": "E1 tile contraction (vec)" * 2, "kernel_ms": 1.51751503943}
+    cfg = {"config": 2, "dtype": "bf16", "ms_per_step": 12.6845123456, "ms_per_step_median": 12.68, "value": 1.234e5,
+           "unit": "GFLOP/s", "roofline": roofline, "einsums": [einsum] * 4, "workload": {"workload": "w" * 400}}
+    out = {"metric": bench.METRIC, "value": 70676.29649914858, "unit": "GFLOP/s", "n_gpus": 1, "steps": 100,
+           "warmup": 5, "ms_per_step": 12.684512345678, "higher_is_better": True, "scaling": "weak",
+           "vs_baseline": None, "dtype": "bf16", "data": "synthetic", "config": cfg["workload"], "roofline": roofline,
+           "cpu_baseline": {"sample": "s" * 300}, "einsums": [einsum] * 4,
+           "timed_region": {"wall_s": 1.25, "ms_per_step_each": [1.2345] * 100}, "configs": [cfg] * 6}
+    line = bench.line_of(out)
+    assert len(json.dumps(line)) < 7000
+    for k in ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling",
+              "vs_baseline", "dtype", "data", "config"):
+        assert line[k] == out[k], k
+    assert line["einsums"][0]["name"] == 123.457 and len(line["configs"]) == 6
+    assert line["timed_region"] == {"wall_s": 1.25}
