@@ -263,28 +263,33 @@ __global__ __launch_bounds__(kThreads) void k_rp_mark(const int32_t* __restrict_
 }
 
 // The marked targets in order, and their number: one workgroup for up to
-// 16384 of them, else from the scanned marks.
-constexpr int kListThreads = 1024, kListPer = 16;
+// 16384 of them, else from the scanned marks.  It has four wavefronts, not
+// sixteen: beside another stream's kernel that fills the chip a CU hardly ever
+// has sixteen places free at once (the stack of a million-vertex chain's rows
+// listed its 4,096 targets only when E1's contraction, 1.4 ms, had ended).
+constexpr int kListThreads = 256, kListMax = 16384;
+template <int PER>  // marks per thread: 16 or 64
 __global__ __launch_bounds__(kListThreads) void k_rp_list_one(const int32_t* __restrict__ marks, int32_t n,
                                                               int32_t* __restrict__ list, RpHeader* __restrict__ hdr) {
     __shared__ int32_t wsum[kListThreads / 64];
-    const int32_t base = int32_t(threadIdx.x) * kListPer;
-    uint32_t there = 0;
+    const int32_t base = int32_t(threadIdx.x) * PER;
+    uint64_t there = 0;
     if (base < n) {
-        // (the table or the rest of the pair list's arrays follow the marks)
-        int4 v[kListPer / 4];
+        // (up to PER - 1 words past the marks are read: the table or the rest
+        // of the pair list's arrays follow)
+        int4 v[PER / 4];
 #pragma unroll
-        for (int i = 0; i < kListPer / 4; i++) v[i] = reinterpret_cast<const int4*>(marks + base)[i];
+        for (int i = 0; i < PER / 4; i++) v[i] = reinterpret_cast<const int4*>(marks + base)[i];
 #pragma unroll
-        for (int i = 0; i < kListPer; i++) {
+        for (int i = 0; i < PER; i++) {
             const int32_t x = i % 4 == 0 ? v[i / 4].x : i % 4 == 1 ? v[i / 4].y : i % 4 == 2 ? v[i / 4].z : v[i / 4].w;
-            if (base + i < n && x) there |= 1u << i;
+            if (base + i < n && x) there |= uint64_t(1) << i;
         }
     }
     int32_t total;
-    int32_t q = block_scan_excl<kListThreads>(__popc(there), wsum, &total);
+    int32_t q = block_scan_excl<kListThreads>(__popcll(there), wsum, &total);
 #pragma unroll
-    for (int i = 0; i < kListPer; i++)
+    for (int i = 0; i < PER; i++)
         if (there >> i & 1) list[q++] = base + i;
     if (threadIdx.x == 0) hdr->n_out = total;
 }
@@ -858,8 +863,10 @@ tre_status tre_repartition(const char* labels, const char* upper_in, const char*
             return dev_fail(e, "header");
         k_rp_mark<<<blocks_for(n_in * d.cover), kThreads, 0, s>>>(keys_in, n_in, d, marks, table, hdr);
         if ((e = hipGetLastError()) != hipSuccess) return dev_fail(e, "marks");
-        if (d.s_out <= kListThreads * kListPer) {
-            k_rp_list_one<<<1, kListThreads, 0, s>>>(marks, int32_t(d.s_out), list, hdr);
+        if (d.s_out <= kListThreads * 16) {
+            k_rp_list_one<16><<<1, kListThreads, 0, s>>>(marks, int32_t(d.s_out), list, hdr);
+        } else if (d.s_out <= kListMax) {
+            k_rp_list_one<64><<<1, kListThreads, 0, s>>>(marks, int32_t(d.s_out), list, hdr);
         } else {
             if ((e = scan_exclusive_i32(marks, marks, d.s_out + 1, reinterpret_cast<int32_t*>(w + L.tmp), s)) !=
                 hipSuccess)

@@ -64,7 +64,7 @@ def test_cells(orc, keep, dtype):
     check(orc, "ij", "ij", "", {"i": 30, "j": 33}, {"i": 5, "j": 11}, {}, dtype, keep)
 
 
-@pytest.mark.parametrize("n_out", [16383, 16384, 16385, 40000])
+@pytest.mark.parametrize("n_out", [255, 4095, 4096, 4097, 16383, 16384, 16385, 40000])
 def test_target_lists(orc, n_out):
     check(orc, "k", "k", "k", {"k": 2 * n_out}, {"k": 1}, {"k": 2}, "f32", 0.6, n_out)
     check(orc, "k", "k", "k", {"k": 2 * n_out}, {"k": 2 * n_out}, {"k": 2}, "bf16", 1.0)
