@@ -5,9 +5,9 @@
 // (split_f32.h), and blocks for which that does not hold are computed again on
 // v_mfma_f32_32x32x2_f32.  A block-sparse product (819 fp32 blocks of 128x128
 // times 16384x1024, 27.5 GFLOP) took 228 us on the fp32 MFMAs (121 TFLOP/s of
-// the 156 they sustain) and takes 155 us: 177 of the 220 TFLOP/s at which
-// registers alone can be split and multiplied (random values hold the bf16
-// MFMAs to 1.69 of 2.46 PFLOP/s by power).
+// the 156 they sustain) and takes 155 to 178 us by run and card: 154 to 177 of
+// the 220 TFLOP/s at which registers alone can be split and multiplied (random
+// values hold the bf16 MFMAs to 1.69 of 2.46 PFLOP/s by power).
 //
 // 256 threads = 4 waves in a 2x2 grid, each wave a 64x64 sub-block (2x2 MFMA
 // tiles, 64 fp32 accumulators per lane).  K advances over the concatenation

@@ -22,10 +22,11 @@
 //
 // Measured against 64 x 64 blocks staged through registers for a workgroup, on
 // the fp32 MFMAs (bf16: two MFMAs a barrier): a chain of 64 x 64 fp32 tiles
-// against 100 columns (67 GFLOP, 1.4 GB) 1030 -> 475 us -- 141 TFLOP/s, 180
-// with the columns' padding to 128; the splitting's vector instructions and the
-// MFMAs, which share the issue slots, bound it at about 220 -- and a bf16
-// product of 96 x 96 blocks with 500 columns (9.2 GFLOP) 128 -> 39 us.
+// against 100 columns (67 GFLOP, 1.4 GB) 1030 -> 450 to 510 us by run and card
+// -- 131 to 148 TFLOP/s, 168 to 190 with the columns' padding to 128; the
+// splitting's vector instructions and the MFMAs, which share the issue slots,
+// bound it at about 220 -- and a bf16 product of 96 x 96 blocks with 500
+// columns (9.2 GFLOP) 128 -> 38 us.
 //
 // How an operand is loaded (chosen in the plan, a template parameter here):
 //   K_RUN   k contiguous: a stage is [row][64 bytes of k]; the 16-byte granule
