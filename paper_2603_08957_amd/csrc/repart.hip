@@ -267,30 +267,37 @@ __global__ __launch_bounds__(kThreads) void k_rp_mark(const int32_t* __restrict_
 // sixteen: beside another stream's kernel that fills the chip a CU hardly ever
 // has sixteen places free at once (the stack of a million-vertex chain's rows
 // listed its 4,096 targets only when E1's contraction, 1.4 ms, had ended).
-constexpr int kListThreads = 256, kListMax = 16384;
-template <int PER>  // marks per thread: 16 or 64
+// A wavefront ballots runs of 64 marks, a thread counts one run.
+constexpr int kListThreads = 256, kListMax = 64 * kListThreads;
 __global__ __launch_bounds__(kListThreads) void k_rp_list_one(const int32_t* __restrict__ marks, int32_t n,
                                                               int32_t* __restrict__ list, RpHeader* __restrict__ hdr) {
     __shared__ int32_t wsum[kListThreads / 64];
-    const int32_t base = int32_t(threadIdx.x) * PER;
-    uint64_t there = 0;
-    if (base < n) {
-        // (up to PER - 1 words past the marks are read: the table or the rest
-        // of the pair list's arrays follow)
-        int4 v[PER / 4];
+    __shared__ uint64_t run[kListThreads];
+    __shared__ int32_t at[kListThreads];
+    constexpr int kWaves = kListThreads / 64, kBatch = 16;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int runs = ((n + 63) / 64 + kWaves - 1) / kWaves, r0 = w * runs;  // of a wavefront, at most 64
+    for (int i0 = 0; i0 < runs; i0 += kBatch) {
+        int32_t x[kBatch];
 #pragma unroll
-        for (int i = 0; i < PER / 4; i++) v[i] = reinterpret_cast<const int4*>(marks + base)[i];
+        for (int i = 0; i < kBatch; i++) x[i] = marks[min((r0 + i0 + i) * 64 + lane, n - 1)];
 #pragma unroll
-        for (int i = 0; i < PER; i++) {
-            const int32_t x = i % 4 == 0 ? v[i / 4].x : i % 4 == 1 ? v[i / 4].y : i % 4 == 2 ? v[i / 4].z : v[i / 4].w;
-            if (base + i < n && x) there |= uint64_t(1) << i;
+        for (int i = 0; i < kBatch; i++) {
+            const uint64_t b = __ballot((r0 + i0 + i) * 64 + lane < n && x[i] != 0);
+            if (lane == 0 && i0 + i < runs) run[r0 + i0 + i] = b;
         }
     }
+    __syncthreads();
     int32_t total;
-    int32_t q = block_scan_excl<kListThreads>(__popcll(there), wsum, &total);
-#pragma unroll
-    for (int i = 0; i < PER; i++)
-        if (there >> i & 1) list[q++] = base + i;
+    at[threadIdx.x] = block_scan_excl<kListThreads>(int(threadIdx.x) < kWaves * runs ? __popcll(run[threadIdx.x]) : 0, wsum,
+                                                    &total);
+    __syncthreads();
+    const uint64_t below = (uint64_t(1) << lane) - 1;
+#pragma unroll 4
+    for (int i = 0; i < runs; i++) {
+        const uint64_t b = run[r0 + i];
+        if (b >> lane & 1) list[at[r0 + i] + __popcll(b & below)] = (r0 + i) * 64 + lane;
+    }
     if (threadIdx.x == 0) hdr->n_out = total;
 }
 
@@ -863,10 +870,8 @@ tre_status tre_repartition(const char* labels, const char* upper_in, const char*
             return dev_fail(e, "header");
         k_rp_mark<<<blocks_for(n_in * d.cover), kThreads, 0, s>>>(keys_in, n_in, d, marks, table, hdr);
         if ((e = hipGetLastError()) != hipSuccess) return dev_fail(e, "marks");
-        if (d.s_out <= kListThreads * 16) {
-            k_rp_list_one<16><<<1, kListThreads, 0, s>>>(marks, int32_t(d.s_out), list, hdr);
-        } else if (d.s_out <= kListMax) {
-            k_rp_list_one<64><<<1, kListThreads, 0, s>>>(marks, int32_t(d.s_out), list, hdr);
+        if (d.s_out <= kListMax) {
+            k_rp_list_one<<<1, kListThreads, 0, s>>>(marks, int32_t(d.s_out), list, hdr);
         } else {
             if ((e = scan_exclusive_i32(marks, marks, d.s_out + 1, reinterpret_cast<int32_t*>(w + L.tmp), s)) !=
                 hipSuccess)
