@@ -750,20 +750,24 @@ struct Unpack {
 // null) its counts: [0] the pairs, [1] the output keys, [2] a tre_status (key
 // errors as on the host, pairs beyond the workspace's capacity), [3] zero.
 // (dn: the counts from the join's header, the host's being bounds)
-// The first red_blocks workgroups sum the partial tiles of split keys (`red`;
-// rh: the header with their number): where only outliers are split, mostly
-// there are none, and a launch of its own would cost 2 us for nothing.
+// RED: the first red_blocks workgroups sum the partial tiles of split keys
+// (`red`; rh: the header with their number): where only outliers are split,
+// mostly there are none, and a launch of its own would cost 2 us for nothing.
+// (An instance of its own: with that code every call's launch takes 0.3 us more.)
+template <bool RED>
 __global__ __launch_bounds__(kThreads) void k_outputs(const uint64_t* __restrict__ seg_key, int64_t n_w, Unpack up, int32_t* __restrict__ w_keys,
                           const int32_t* __restrict__ pu, const int32_t* __restrict__ pv, int64_t n_pairs,
                           int32_t* __restrict__ pairs, const WsHeader* __restrict__ dn, int64_t max_pairs,
                           int64_t* __restrict__ counts, Reduction red, int32_t red_blocks,
                           const WsHeader* __restrict__ rh) {
-    if (int32_t(blockIdx.x) < red_blocks) {
-        const int64_t per = reduce_blocks(red.w_elems), all = int64_t(rh->n_split) * per;
-        for (int64_t b = blockIdx.x; b < all; b += red_blocks) reduce_key(red, b / per, b % per, per);
-        return;
+    if constexpr (RED) {
+        if (int32_t(blockIdx.x) < red_blocks) {
+            const int64_t per = reduce_blocks(red.w_elems), all = int64_t(rh->n_split) * per;
+            for (int64_t b = blockIdx.x; b < all; b += red_blocks) reduce_key(red, b / per, b % per, per);
+            return;
+        }
     }
-    const int64_t i = int64_t(blockIdx.x - red_blocks) * blockDim.x + threadIdx.x;
+    const int64_t i = int64_t(blockIdx.x - (RED ? red_blocks : 0)) * blockDim.x + threadIdx.x;
     if (counts && i == 0) {
         auto key_status = [](int32_t f) {
             return (f & 4) ? int64_t(TRE_E_KEYRANGE) : (f & 1) ? int64_t(TRE_E_UNSORTED) : (f & 2) ? int64_t(TRE_E_DUPKEY) : 0;
@@ -1009,7 +1013,8 @@ hipError_t launch_write_outputs(const Plan& p, const Layout& L, char* ws, int32_
     up.n = p.nk[2];
     for (int c = 0; c < p.nk[2]; c++) up.bits[c] = p.w_bits[c];
     const WsHeader* hdr = reinterpret_cast<const WsHeader*>(ws + L.hdr);
-    k_outputs<<<blocks_for(n) + unsigned(red_blocks), kThreads, 0, s>>>(
+    const auto kernel = red_blocks > 0 ? k_outputs<true> : k_outputs<false>;
+    kernel<<<blocks_for(n) + unsigned(red_blocks), kThreads, 0, s>>>(
         reinterpret_cast<const uint64_t*>(ws + L.seg_key), n_w, up, w_keys, reinterpret_cast<const int32_t*>(ws + L.pu),
         reinterpret_cast<const int32_t*>(ws + L.pv), n_pairs, pairs_out, dev_counts ? hdr : nullptr, L.max_pairs, counts,
         reduction(p, L, ws, reduce_into), red_blocks, hdr);
